@@ -646,7 +646,8 @@ def main():
     seconds = wall
     mlups = nsite * args.steps / seconds / 1e6
     col_avg_ms = col_ms / max(col_n, 1)
-    achieved = alg["collide"] * nsite / (col_avg_ms * 1e-3) / 1e9
+    # a single-fluid launch may hold two steps: bytes of all steps over all launches' time
+    achieved = alg["collide"] * nsite * args.steps / (col_ms * 1e-3) / 1e9 if col_n else 0.0
     step_bytes = alg["collide"]
 
     out = {
@@ -667,6 +668,7 @@ def main():
         "roofline": {
             "bound": "hbm",
             "kernel": ("k_binary_march (single-pass pull-stream + phi + collision)" if model == "binary"
+                       else "k_single_pair (two fused pull-stream + collision steps a launch)" if col_n < args.steps
                        else "k_collide (fused pull-stream + collision)"),
             "achieved": round(achieved, 1),
             "peak": HBM_PEAK_GBS,

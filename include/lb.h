@@ -185,8 +185,12 @@ int lb_collide(lb_ctx* ctx);
 int lb_propagate(lb_ctx* ctx);
 
 /* nsteps x (collide; propagate).  nsteps == 0 is a no-op, < 0 is LB_EINVAL.
- * Each step is one launch of a fused pull-stream + collide kernel: for
- * LB_BINARY on large lattices the single-pass march, which sums phi from
+ * Each step is one launch of a fused pull-stream + collide kernel.  For
+ * LB_SINGLE with vvl 0 or 1, lattices from 48000 (LB_F64), 200000 (LB_F32) or
+ * 850000 (LB_F16) sites take their steps two to a launch, the state between
+ * them staying on chip (an odd last step runs alone); the bits are the same,
+ * and LB_K_COLLIDE then counts a pair as one launch.  For
+ * LB_BINARY on large lattices it is the single-pass march, which sums phi from
  * the pulled g and takes its stencils on chip; on small lattices (or with
  * LB_STEP_TWO_PASS) a phi kernel, then the fused collide (see
  * binary_step).  Paper: Section IV (collision) and Section II-A

@@ -201,25 +201,27 @@ __device__ __forceinline__ Site site_at(const Column& c, int v, const Geo& g) {
 // elements once ran 20-30% slower in the 32-bit form, because a running sum
 // over 19 gathered values then sent its loads out one at a time; with the
 // values gathered into an array before the sum it is 1% faster for them.)
-template <class S>
+// WIDE is the element form; the default is the one described above, and a
+// kernel that is launched apart for arrays below and beyond 4 GiB names it.
+template <class S, bool WIDE = sizeof(S) == 4>
 __device__ __forceinline__ const S* at(const S* base, uint32_t off) {
-    if constexpr (sizeof(S) == 4) return base + off;
+    if constexpr (WIDE) return base + off;
     else return reinterpret_cast<const S*>(reinterpret_cast<const char*>(base) + (uint32_t)(off * (uint32_t)sizeof(S)));
 }
-template <class S>
+template <class S, bool WIDE = sizeof(S) == 4>
 __device__ __forceinline__ S* at(S* base, uint32_t off) {
-    if constexpr (sizeof(S) == 4) return base + off;
+    if constexpr (WIDE) return base + off;
     else return reinterpret_cast<S*>(reinterpret_cast<char*>(base) + (uint32_t)(off * (uint32_t)sizeof(S)));
 }
-template <bool NT, class S>
+template <bool NT, class S, bool WIDE = sizeof(S) == 4>
 __device__ __forceinline__ S ldg(const S* base, uint32_t off) {
-    const S* p = at(base, off);
+    const S* p = at<S, WIDE>(base, off);
     if constexpr (NT) return __builtin_nontemporal_load(p);
     else return *p;
 }
-template <bool NT, class S>
+template <bool NT, class S, bool WIDE = sizeof(S) == 4>
 __device__ __forceinline__ void stg(S* base, uint32_t off, S v) {
-    S* p = at(base, off);
+    S* p = at<S, WIDE>(base, off);
     if constexpr (NT) __builtin_nontemporal_store(v, p);
     else *p = v;
 }

@@ -90,13 +90,13 @@ struct FreeEnergy {
 
 // Load the 19 populations of one site (pulled from s - c_i when GATHER) from
 // direction arrays `stride` elements apart (default: the lattice's own).
-template <class P, bool GATHER, class S, class T>
+template <class P, bool GATHER, class S, class T, bool WIDE = sizeof(S) == 4>
 __device__ __forceinline__ void load_site(const S* src, const Site& st, const Geo& geo, T (&v)[Q],
                                           int64_t stride = -1) {
     const int64_t ds = stride < 0 ? geo.dstride : stride;
     static_for<0, Q>([&](auto I) {
         constexpr int i = decltype(I)::value;
-        v[i] = static_cast<T>(ldg<P::nt_load>(src + i * ds, src_offset<i, GATHER>(st, geo)));
+        v[i] = static_cast<T>(ldg<P::nt_load, S, WIDE>(src + i * ds, src_offset<i, GATHER>(st, geo)));
     });
 }
 
@@ -206,39 +206,93 @@ __device__ __forceinline__ void relax_moments_store(const T (&f)[Q], const T (&n
     });
 }
 
-template <class P, int COLL = COLL_BGK, class S, class T>
-__device__ __forceinline__ void relax_single(const T (&f)[Q], S* fdst, uint32_t off, const Geo& geo,
-                                             const CollParams<T>& cp, int64_t stride = -1) {
-    const int64_t ds = stride < 0 ? geo.dstride : stride;
+// Collision of one site of the single fluid, f -> f*.  Every rounding is
+// written out (fma where one is wanted, no contraction left to the compiler),
+// so each kernel that collides a site gives the same bits whatever surrounds
+// the call: a state does not depend on whether its steps ran one or two to a
+// launch, or were recorded.
+template <class T>
+__device__ __forceinline__ T fma_(T a, T b, T c) { return __builtin_elementwise_fma(a, b, c); }
+
+// v rounded to the storage type, v itself first pinned in a register.  For
+// binary16, an fma whose result is only ever stored may otherwise become one
+// mixed-precision instruction that rounds once, and which of them do differs
+// from kernel to kernel; and where a store is conditional the value is
+// otherwise formed again behind each condition (25 VGPRs spilled in the
+// FP32 MRT pair kernel without the pin, none with it).
+template <class S, class T>
+__device__ __forceinline__ S stored(T v) {
+    asm("" : "+v"(v));
+    return static_cast<S>(v);
+}
+
+template <int COLL, class S, class T>
+__device__ __forceinline__ void collide_single(const T (&f)[Q], T (&out)[Q], const CollParams<T>& cp) {
+#pragma clang fp contract(off)
     T drho, jx, jy, jz;
     moments_in<typename Accum<S>::T>(f, drho, jx, jy, jz);
     const T rho = cp.rho0 + drho;
     const T ux = jx / rho, uy = jy / rho, uz = jz / rho;
-    const T usq = ux * ux + uy * uy + uz * uz;
-    if constexpr (COLL != COLL_BGK) {
-        T neq[Q];
+    const T usq = T(-1.5) * fma_(uz, uz, fma_(uy, uy, ux * ux));
+    const auto neq_of = [&](auto I) {
+#pragma clang fp contract(off)
+        constexpr int i = decltype(I)::value;
+        const T cu = cdot<i>(ux, uy, uz);
+        const T base = fma_(T(3), cu, fma_(T(4.5) * cu, cu, usq));
+        return fma_(-weight<T>(i), fma_(rho, base, drho), f[i]);
+    };
+    if constexpr (COLL == COLL_BGK) {
         static_for<0, Q>([&](auto I) {
             constexpr int i = decltype(I)::value;
-            const T cu = cdot<i>(ux, uy, uz);
-            neq[i] = f[i] - weight<T>(i) * (drho + rho * (T(3) * cu + T(4.5) * cu * cu - T(1.5) * usq));
+            out[i] = fma_(-cp.omega_f, neq_of(I), f[i]);
         });
-        relax_moments_store<P, COLL>(f, neq, fdst, off, ds, cp);
     } else {
-        // every post-collision value before the first store (measured 1.3%
-        // faster than storing each as it is computed)
-        T out[Q];
+        T neq[Q];
+        static_for<0, Q>([&](auto I) { neq[decltype(I)::value] = neq_of(I); });
+        T a[7] = {T(0), T(0), T(0), T(0), T(0), T(0), T(0)};
+        if constexpr (COLL == COLL_MRT) {
+            static_for<0, 7>([&](auto K) {
+#pragma clang fp contract(off)
+                constexpr int k = decltype(K)::value;
+                T acc = T(0);
+                static_for<0, Q>([&](auto I) {
+                    constexpr int i = decltype(I)::value;
+                    constexpr int c = mrt_poly(mrt_extra(k), i);
+                    if constexpr (c != 0) acc = fma_(T(c), neq[i], acc);
+                });
+                // k = 0: energy (bulk); 1-3: eps, pi_xx, pi_ww (even ghosts); 4-6: m (odd ghosts)
+                const T dw = k == 0 ? cp.omega_b - cp.omega_f : (k < 4 ? cp.omega_ge - cp.omega_f : cp.omega_go - cp.omega_m);
+                a[k] = dw * (T(1) / T(mrt_norm(mrt_extra(k)))) * acc;
+            });
+        }
         static_for<0, Q>([&](auto I) {
+#pragma clang fp contract(off)
             constexpr int i = decltype(I)::value;
-            const T cu = cdot<i>(ux, uy, uz);
-            const T base = T(3) * cu + T(4.5) * cu * cu - T(1.5) * usq;
-            const T feq = weight<T>(i) * (drho + rho * base);
-            out[i] = f[i] - cp.omega_f * (f[i] - feq);
-        });
-        static_for<0, Q>([&](auto I) {
-            constexpr int i = decltype(I)::value;
-            stg<P::nt_store>(fdst + i * ds, off, static_cast<S>(out[i]));
+            constexpr int o = opp(i);
+            T r = fma_(cp.omega_f, T(0.5) * (neq[i] + neq[o]), cp.omega_m * (T(0.5) * (neq[i] - neq[o])));
+            if constexpr (COLL == COLL_MRT) {
+                static_for<0, 7>([&](auto K) {
+                    constexpr int k = decltype(K)::value;
+                    constexpr int c = mrt_poly(mrt_extra(k), i);
+                    if constexpr (c != 0) r = fma_(T(c), a[k], r);
+                });
+            }
+            out[i] = f[i] - r;
         });
     }
+}
+
+// collide_single, stored: every post-collision value before the first store
+// (measured 1.3% faster than storing each as it is computed).
+template <class P, int COLL = COLL_BGK, class S, class T>
+__device__ __forceinline__ void relax_single(const T (&f)[Q], S* fdst, uint32_t off, const Geo& geo,
+                                             const CollParams<T>& cp) {
+    T out[Q];
+    collide_single<COLL, S>(f, out, cp);
+    static_for<0, Q>([&](auto I) {
+        constexpr int i = decltype(I)::value;
+        stg<P::nt_store>(fdst + i * geo.dstride, off, stored<S>(out[i]));
+    });
 }
 
 // Binary collision of one site: g relaxes with omega_g (BGK); f with BGK, or
@@ -525,6 +579,142 @@ __global__ __launch_bounds__(P::TPB) void k_binary_march(const S* __restrict__ f
             for (int i = 0; i < Q; ++i) gc[i] = gn[i];
         }
         if constexpr (RING == 3) __syncthreads();
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Two single-fluid steps in one pass over memory.  A step on its own reads
+// and writes every value once and runs at the rate of a plain copy, so only
+// fewer bytes make it faster: here the state between the two steps never
+// leaves the chip, and a pair of steps moves the bytes of one.
+//
+// A block owns a TX x TY column tile and marches through a chunk of z planes.
+// Each lane collides its site of plane p (step one).  The 16 values with c_x
+// or c_y nonzero go through LDS to the lane of the site they stream to; one
+// lane each also collides the 2 TX + 2 TY + 4 sites around the tile, whose
+// values stream in.  What streams up or down (c_z) waits in registers: a
+// site of plane p - 1 takes its c_z < 0 values from plane p, the c_z = 0 ones
+// kept from plane p - 1 and the c_z > 0 ones kept from p - 2, so 19 values
+// are kept in all, and is then collided and stored (step two).  A chunk needs
+// one extra plane of step one at either end.  The values between the steps
+// are rounded to the storage type, so the result has the bits of two steps.
+//
+// The next plane's loads are issued before step two, whose arithmetic and
+// stores cover their latency (FP64 256^3: 1.04 ms a pair, 1.05 with a second
+// barrier per plane instead of two LDS buffers, 1.07 without early loads but
+// two blocks a CU; two single steps take 1.79).  Loading the ring's values
+// early too costs registers: 2% faster in FP64 at 256^3, 5-8% slower at 128^3
+// and 160^3.  Halves of a wavefront (32-wide tiles) and 64 x 4 tiles lose
+// 6-10% at 256^3, 64 x 16 5%.
+//
+// REC: post-collision values of step one are stored as well, to `mid`.
+// ---------------------------------------------------------------------------
+
+// LDS slot of direction i among those with c_x or c_y nonzero.
+__host__ __device__ constexpr int planar_slot(int i) {
+    int n = 0;
+    for (int j = 0; j < i; ++j) n += (cx(j) != 0 || cy(j) != 0) ? 1 : 0;
+    return n;
+}
+static_assert(planar_slot(Q) == 16, "directions that leave the column");
+
+template <class P, class S, bool GATHER, int COLL, bool BLK, bool WIDE, bool REC>
+__global__ __launch_bounds__(P::TPB, sizeof(S) == 8 ? 2 : 4) void k_single_pair(
+    const S* __restrict__ src, S* __restrict__ mid, S* __restrict__ dst, Geo geo_in,
+    CollParams<typename Compute<S>::T> cp) {
+    using T = typename Compute<S>::T;
+    Geo geo = geo_in;
+    if constexpr (BLK) geo.dstride = 64;
+    constexpr int TX = P::TX, TY = P::TY, NRING = 2 * TX + 2 * TY + 4;
+    static_assert(NRING <= P::TPB, "one ring site per lane");
+    __shared__ S moved[2][16][P::TPB];
+
+    // tiles in XCD order for any count: the grid is rounded up to a multiple
+    // of 8 and the surplus blocks leave at once
+    const int b = (int)((blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3));
+    if (b >= geo.nblocks) return;
+    const int bx = b % geo.gx;
+    const int by = (b / geo.gx) % geo.gy;
+    const int zc = b / (geo.gx * geo.gy);
+    const int z0 = (int)((int64_t)zc * geo.nz / geo.gz), z1 = (int)((int64_t)(zc + 1) * geo.nz / geo.gz);
+    const int x0 = bx * TX, y0 = by * TY;
+    const int t = threadIdx.x, tx = t % TX, ty = t / TX;
+    const bool active = (x0 + tx < geo.nx) && (y0 + ty < geo.ny);
+    // the lane just outside a ragged tile holds the periodic neighbour; those
+    // further out repeat it (nothing they compute is used)
+    const int x = x0 + tx < geo.nx ? x0 + tx : 0, y = y0 + ty < geo.ny ? y0 + ty : 0;
+
+    // this lane's ring site, if any: (rx, ry) in the tile's coordinates
+    int rx, ry;
+    if (t < 2 * TX) { rx = t % TX; ry = t < TX ? -1 : TY; }
+    else if (t < 2 * TX + 2 * TY) { rx = t < 2 * TX + TY ? -1 : TX; ry = (t - 2 * TX) % TY; }
+    else { rx = (t & 1) ? TX : -1; ry = (t & 2) ? TY : -1; }
+    const bool ring = t < NRING;
+    const int gx = x0 + rx, gy = y0 + ry;
+    const int xr = gx < 0 ? geo.nx - 1 : (gx < geo.nx ? gx : 0), yr = gy < 0 ? geo.ny - 1 : (gy < geo.ny ? gy : 0);
+
+    T f[Q];
+    load_site<P, GATHER, S, T, WIDE>(src, site_wrapped(x, y, wrap_plane(z0 - 1, geo.nz), geo), geo, f);
+    T level[9], rise1[5], rise2[5];      // kept: c_z = 0 and c_z > 0 of plane p - 1, c_z > 0 of plane p - 2
+#pragma unroll
+    for (int k = 0; k < 9; ++k) level[k] = T(0);
+#pragma unroll
+    for (int k = 0; k < 5; ++k) rise1[k] = rise2[k] = T(0);
+
+    for (int p = z0 - 1; p <= z1; ++p) {
+        S (*lds)[P::TPB] = moved[(p - z0) & 1];
+        const int pw = wrap_plane(p, geo.nz);
+        auto send = [&](const T (&o)[Q], int ox, int oy) {
+            static_for<0, Q>([&](auto I) {
+                constexpr int i = decltype(I)::value;
+                if constexpr (cx(i) != 0 || cy(i) != 0) {
+                    const int dx = ox + cx(i), dy = oy + cy(i);
+                    if (dx >= 0 && dx < TX && dy >= 0 && dy < TY) lds[planar_slot(i)][dy * TX + dx] = stored<S>(o[i]);
+                }
+            });
+        };
+        T o[Q];
+        collide_single<COLL, S>(f, o, cp);
+        send(o, tx, ty);
+        if constexpr (REC) {
+            if (active && p >= z0 && p < z1) {
+                const uint32_t off = offset_at<0, 0, 0>(site_wrapped(x, y, p, geo), geo);
+                static_for<0, Q>([&](auto I) {
+                    constexpr int i = decltype(I)::value;
+                    stg<P::nt_store, S, WIDE>(mid + i * geo.dstride, off, stored<S>(o[i]));
+                });
+            }
+        }
+        if (ring) {
+            T r[Q], ro[Q];
+            load_site<P, GATHER, S, T, WIDE>(src, site_wrapped(xr, yr, pw, geo), geo, r);
+            collide_single<COLL, S>(r, ro, cp);
+            send(ro, rx, ry);
+        }
+        __syncthreads();     // two buffers: plane p + 2 writes this one only after the next barrier
+        T g[Q];
+        static_for<0, Q>([&](auto I) {
+            constexpr int i = decltype(I)::value;
+            if constexpr (cx(i) != 0 || cy(i) != 0) g[i] = static_cast<T>(lds[planar_slot(i)][t]);
+            else g[i] = static_cast<T>(stored<S>(o[i]));
+        });
+        if (p < z1) load_site<P, GATHER, S, T, WIDE>(src, site_wrapped(x, y, wrap_plane(p + 1, geo.nz), geo), geo, f);
+        T f2[Q];
+        int ku = 0, kl = 0;
+        static_for<0, Q>([&](auto I) {
+            constexpr int i = decltype(I)::value;
+            if constexpr (cz(i) > 0) { f2[i] = rise2[ku]; rise2[ku] = rise1[ku]; rise1[ku] = g[i]; ++ku; }
+            else if constexpr (cz(i) == 0) { f2[i] = level[kl]; level[kl] = g[i]; ++kl; }
+            else f2[i] = g[i];
+        });
+        if (p > z0 && active) {
+            collide_single<COLL, S>(f2, o, cp);
+            const uint32_t off = offset_at<0, 0, 0>(site_wrapped(x, y, p - 1, geo), geo);
+            static_for<0, Q>([&](auto I) {
+                constexpr int i = decltype(I)::value;
+                stg<P::nt_store, S, WIDE>(dst + i * geo.dstride, off, stored<S>(o[i]));
+            });
+        }
     }
 }
 

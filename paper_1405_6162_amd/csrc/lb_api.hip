@@ -76,6 +76,37 @@ template <> struct March<_Float16> {
 // (block count a multiple of 8), else into chunks of the depth and a shorter
 // last one.
 constexpr int kMarchSlots = 512;
+// Two single-fluid steps per launch (k_single_pair): the tiles per storage
+// type and how many blocks a CU holds (FP64: 128 KB of LDS and up to 256
+// VGPRs a lane, one 512-lane block; FP32 and FP16: 128 VGPRs, two blocks of
+// 64 x 8 or one of 128 x 8).  As in the march, the 128-wide tile W is used
+// where its rows leave no more lanes idle: at 256^3 490 against 559 us a pair
+// in FP32 and 355 against 384 in FP16, equal at 96^3.
+// kPairMinSites: below it a pair costs more than two single steps, whose
+// blocks each do one plane where a pair's lead in and out over three.  us a
+// pair, one pair launch / two single ones: FP64 32^3 11.7 / 8.8, 40^3 11.8 /
+// 13.0, 48^3 15.9 / 17.6, 64^3 21.5 / 33.9; FP32 48^3 12.3 / 10.8, 64^3 12.9 /
+// 19.2; FP16 80^3 26.9 / 25.9, 300 x 9 x 300 35.4 / 31.4, 96^3 31.0 / 37.1.
+constexpr int kCUs = 256;
+template <class S> struct Pair;
+template <> struct Pair<double> {
+    using P = Tiling<64, 8, 1, false, true, true>;
+    using W = P;
+    static constexpr int64_t min_sites = 48000;
+};
+template <> struct Pair<float> {
+    using P = Tiling<64, 8, 1, false, true, true>;
+    using W = Tiling<128, 8, 1, false, true, true>;
+    static constexpr int64_t min_sites = 200000;
+};
+template <> struct Pair<_Float16> {
+    using P = Tiling<64, 8, 1, false, true, true>;
+    using W = Tiling<128, 8, 1, false, true, true>;
+    static constexpr int64_t min_sites = 850000;
+};
+// Blocks of k_single_pair a CU holds at once.
+template <class S, class TP>
+constexpr int pair_blocks_per_cu() { return sizeof(S) == 8 ? 1 : 1024 / TP::TPB; }
 
 constexpr size_t kAlign = 4096;
 // Extra bytes between consecutive direction arrays, so the 19 (38) streams of
@@ -260,6 +291,28 @@ struct lb_ctx {
             g.bz = tiles(p.nz, chunks);
         }
         g.gz = tiles(p.nz, g.bz);
+        g.nblocks = g.gx * g.gy * g.gz;
+        return g;
+    }
+    // Tiling of the pair kernel.  A chunk of d planes takes d + 2 planes of
+    // step one and about one more of prologue, and the chip runs `slots`
+    // blocks at a time: nz is cut into the number of chunks (at most 128
+    // planes each) that makes rounds x (d + 3) least.  256^3 FP64: 926 us a
+    // pair with 2 chunks (one round) against 1045 with 4; 128^3: 128 with 8
+    // (one round) against 145 with 16.
+    template <class TP>
+    Geo pair_geo(int slots) const {
+        Geo g = geo();
+        g.gx = tiles(p.nx, TP::TX);
+        g.gy = tiles(p.ny, TP::TY);
+        const int64_t col = (int64_t)g.gx * g.gy;
+        int64_t best = INT64_MAX;
+        g.gz = 1;
+        for (int c = tiles(p.nz, 128); c <= p.nz; ++c) {
+            const int64_t cost = (col * c + slots - 1) / slots * (tiles(p.nz, c) + 3);
+            if (cost < best) { best = cost; g.gz = c; }
+        }
+        g.bz = tiles(p.nz, g.gz);
         g.nblocks = g.gx * g.gy * g.gz;
         return g;
     }
@@ -499,8 +552,64 @@ int run_propagate(lb_ctx* c) {
     return LB_OK;
 }
 
+// Calls fn with the context's collision as an integral constant.
+template <class F>
+void by_collision(const lb_ctx* c, F&& fn) {
+    if (c->p.collision == LB_TRT) fn(std::integral_constant<int, COLL_TRT>{});
+    else if (c->p.collision == LB_MRT) fn(std::integral_constant<int, COLL_MRT>{});
+    else fn(std::integral_constant<int, COLL_BGK>{});
+}
+
+// Two collisions, with the propagation between them, of the state in `src`
+// (a pending one is pulled), into `dst`; REC: the first one's values into
+// `mid`.  All three in the layout of geo().
+template <class S, bool BLK, bool WIDE, bool REC>
+int launch_single_pair(lb_ctx* c, bool pending, const S* src, S* mid, S* dst, bool canonical) {
+    using PP = typename Pair<S>::P;
+    using PW = typename Pair<S>::W;
+    const auto cp = coll_params<S>(c);
+    const bool wide = tiles(c->p.nx, PW::TX) * PW::TX == tiles(c->p.nx, PP::TX) * PP::TX;
+    auto launch = [&](auto tiling) {
+        using TP = decltype(tiling);
+        Geo g = c->template pair_geo<TP>(kCUs * pair_blocks_per_cu<S, TP>());
+        if (canonical) g = c->canonical(g);
+        const dim3 grid((unsigned)((g.nblocks + 7) / 8 * 8)), block(TP::TPB);
+        Timed t(c, LB_K_COLLIDE);
+        by_collision(c, [&](auto coll) {
+            constexpr int COLL = decltype(coll)::value;
+            if (pending) k_single_pair<TP, S, true, COLL, BLK, WIDE, REC><<<grid, block, 0, c->stream>>>(src, mid, dst, g, cp);
+            else k_single_pair<TP, S, false, COLL, BLK, WIDE, REC><<<grid, block, 0, c->stream>>>(src, mid, dst, g, cp);
+        });
+    };
+    if (wide) launch(PW{});
+    else launch(PP{});
+    return launch_status();
+}
+
+// Whether two single-fluid steps run as one launch: not with more than one
+// site per lane (lb_params.vvl), nor on lattices too small or too large for
+// the blocked layout.
+template <class S>
+bool pair_pays(const lb_ctx* c) {
+    return c->p.model == LB_SINGLE && c->p.vvl <= 1 && c->L.blocked && c->L.nsite >= Pair<S>::min_sites;
+}
+
 template <class S>
 int run_step(lb_ctx* c, int32_t n) {
+    if (pair_pays<S>(c)) {
+        // 4-byte states pass 4 GiB and stay blocked; the others do not
+        const bool wide = sizeof(S) == 4 && c->L.dist_bytes >= ((size_t)1 << 32);
+        for (; n >= 2; n -= 2) {
+            const S* src = (const S*)c->fbuf(c->cur);
+            S* dst = (S*)c->fbuf(1 - c->cur);
+            int rc;
+            if (wide) rc = launch_single_pair<S, true, true, false>(c, c->pending, src, nullptr, dst, false);
+            else rc = launch_single_pair<S, true, false, false>(c, c->pending, src, nullptr, dst, false);
+            if (rc) return rc;
+            c->cur = 1 - c->cur;
+            c->pending = true;
+        }
+    }
     for (int32_t k = 0; k < n; ++k) {
         int rc = run_collide<S>(c);
         if (rc) return rc;

@@ -1,0 +1,78 @@
+"""Two single-fluid steps per launch (k_single_pair).
+
+lb_step pairs its steps where the lattice is large enough; one step at a
+time it never does, so n single-step calls are the reference: the collision
+is written with explicit roundings, and the same bits are expected.  The
+shapes sit at the edges of the kernel's tiles (64 x 8 columns; 128 x 8 in
+FP32 and FP16 where nx mod 128 is 0 or above 64) and chunks: one site over,
+one short, exact, an extent of one and of two, several rounds of chunks.
+Odd step counts end with a single step; a count of 2 from a fresh state
+starts from a direct (unpropagated) one, 3 + 4 from a pending one.  One case
+is held to the C oracle as well (FP64, 1e-12 relative to the largest value,
+the bound every FP64 path is held to).
+"""
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import c_backend as C
+from paper_1405_6162_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = {
+    "f64": [(67, 9, 80), (64, 8, 96), (129, 25, 17), (1, 223, 217), (2, 160, 155), (63, 7, 111), (256, 200, 1),
+            (128, 250, 2)],
+    "f32": [(67, 45, 67), (128, 40, 40), (127, 33, 49), (193, 41, 26), (320, 320, 2)],
+    "f16": [(150, 70, 90), (128, 83, 81), (129, 65, 103)],
+}
+COLL = {"bgk": {}, "trt": dict(collision=1, tau_minus=1.25),
+        "mrt": dict(collision=2, tau_minus=1.25, tau_bulk=1.4, tau_ghost_even=0.9, tau_ghost_odd=1.2)}
+
+
+def _fields(nx, ny, nz):
+    return inputs.single_fluid_random(nx, ny, nz, seed=nx + ny)
+
+
+@pytest.mark.parametrize("coll", ["bgk", "trt", "mrt"])
+@pytest.mark.parametrize("storage,nx,ny,nz", [(s,) + n for s in SHAPES for n in SHAPES[s]])
+def test_pairs_equal_single_steps(lbgpu, storage, nx, ny, nz, coll):
+    print("case single %dx%dx%d %s %s, pairs vs single steps" % (nx, ny, nz, storage, coll), flush=True)
+    code = {"f64": lbgpu.LB_F64, "f32": lbgpu.LB_F32, "f16": lbgpu.LB_F16}[storage]
+    rho, u = _fields(nx, ny, nz)
+    got = {}
+    for how in ("pairs", "steps"):
+        lat = lbgpu.Lattice(nx, ny, nz, storage=code, tau_f=0.8, **COLL[coll])
+        lat.init_equilibrium(rho, u)
+        lbgpu.lb_profile(lat.ctx, True)
+        states = []
+        for n in (2, 3, 4):
+            for k in ([n] if how == "pairs" else [1] * n):
+                lat.step(k)
+            states.append(lat.get_state()[0])
+        lbgpu.lb_profile(lat.ctx, False)
+        launches = lbgpu.lb_kernel_times(lat.ctx, lbgpu.LB_K_COLLIDE)[1]
+        assert launches == (5 if how == "pairs" else 9)
+        lat.close()
+        got[how] = states
+    for a, b in zip(got["pairs"], got["steps"]):
+        assert bool(torch.isfinite(a).all()) and torch.equal(a, b)
+
+
+def test_pairs_against_oracle(lbgpu):
+    nx, ny, nz = 67, 9, 80
+    print("case single %dx%dx%d FP64 x5, pairs vs C oracle" % (nx, ny, nz), flush=True)
+    rho, u = _fields(nx, ny, nz)
+    C.set_threads(0)
+    ref = C.CLattice(nx, ny, nz, model=0)
+    ref.init_equilibrium(rho, u)
+    ref.step(5)
+    want = ref.state()[0]
+    ref.close()
+    lat = lbgpu.Lattice(nx, ny, nz)
+    lat.init_equilibrium(rho, u)
+    lat.step(5)
+    f = lat.get_state()[0].cpu().numpy()
+    lat.close()
+    assert np.abs(f - want).max() <= 1e-12 * np.abs(want).max()
