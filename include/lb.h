@@ -186,8 +186,8 @@ int lb_propagate(lb_ctx* ctx);
 
 /* nsteps x (collide; propagate).  nsteps == 0 is a no-op, < 0 is LB_EINVAL.
  * Each step is one launch of a fused pull-stream + collide kernel.  For
- * LB_SINGLE with vvl 0 or 1, lattices from 48000 (LB_F64), 200000 (LB_F32) or
- * 850000 (LB_F16) sites take their steps two to a launch, the state between
+ * LB_SINGLE with vvl 0 or 1, lattices from 130000 (LB_F64), 200000 (LB_F32) or
+ * 2000000 (LB_F16, nx a multiple of 64 and ny of 8) sites take their steps two to a launch, the state between
  * them staying on chip (an odd last step runs alone); the bits are the same,
  * and LB_K_COLLIDE then counts a pair as one launch.  For
  * LB_BINARY on large lattices it is the single-pass march, which sums phi from

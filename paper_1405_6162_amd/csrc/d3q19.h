@@ -111,7 +111,6 @@ struct Geo {
     int gx, gy, gz;     // tiles along x, y and z
     int nblocks;        // gx * gy * gz: the 1-D grid size
     uint32_t zs, ys, xbs;   // site-offset strides of the distribution layout
-    int bz;             // z planes per block of the single-pass march (its chunk depth)
 };
 
 // Launch policy.  A block covers TX x TY x TZ sites; each lane owns one
@@ -157,6 +156,52 @@ __device__ __forceinline__ int tile_index(const Geo& g) {
     if (xcd_remapped<P>(g)) b = (b & 7) * (g.nblocks >> 3) + (b >> 3);
     return b;
 }
+
+// Tile and chunk of planes of a marching kernel's block; false for the
+// surplus blocks of a grid rounded up to a multiple of 8: block b takes tile
+// (b mod 8) * grid/8 + b/8, so each XCD sweeps a contiguous run of tiles for
+// any count.  (Without the rounding 150 x 70 x 90, whose count is no multiple
+// of 8, lost its neighbours' lines in L2: a single-fluid FP32 pair took 51 us
+// there instead of 36.)  The geo.gz chunks split nz evenly.
+//
+// A last column less than full leaves lanes idle.  Narrower tiles for it (32,
+// 16 and 8 wide, by the digits of what is left) were measured and are worse:
+// a wavefront of an 8-wide tile touches eight rows with every load, and its
+// blocks then outlast all others (march, FP64 200 x 204 x 100 840 against 556
+// us, 96^3 in FP32 61 against 44).
+struct TileAt { int x0, y0, z0, z1; };
+
+template <class P>
+__device__ __forceinline__ bool tile_of_block(const Geo& g, TileAt& r) {
+    const int b = (int)((blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3));
+    if (b >= g.nblocks) return false;
+    const int zc = b / (g.gx * g.gy);
+    r.x0 = b % g.gx * P::TX;
+    r.y0 = b / g.gx % g.gy * P::TY;
+    r.z0 = (int)((int64_t)zc * g.nz / g.gz);
+    r.z1 = (int)((int64_t)(zc + 1) * g.nz / g.gz);
+    return true;
+}
+
+// Lane k's place, if it has one, in the ring of sites around a tile, in the
+// tile's coordinates.  The ring is taken in order, the rows above and below
+// first, so those land on whole wavefronts and load contiguously (measured
+// faster than spreading the ring over all wavefronts); the four corners, last,
+// only with CORNERS.
+template <class P, bool CORNERS>
+__device__ __forceinline__ bool ring_site(int k, int& rx, int& ry) {
+    constexpr int TX = P::TX, TY = P::TY;
+    if (k < 2 * TX) { rx = k % TX; ry = k < TX ? -1 : TY; return true; }
+    k -= 2 * TX;
+    if (k < 2 * TY) { rx = k < TY ? -1 : TX; ry = k % TY; return true; }
+    k -= 2 * TY;
+    rx = (k & 1) ? TX : -1;
+    ry = (k & 2) ? TY : -1;
+    return CORNERS && k < 4;
+}
+// Periodic image of a coordinate in [-1, n + tile); beyond n it repeats 0:
+// only a lane just outside a ragged tile is asked for its value.
+__device__ __forceinline__ int image_of(int x, int n) { return x < 0 ? n - 1 : (x < n ? x : 0); }
 
 template <class P>
 __device__ __forceinline__ Column column_of_thread(const Geo& g) {

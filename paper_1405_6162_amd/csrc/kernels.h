@@ -164,122 +164,118 @@ __global__ __launch_bounds__(P::TPB) void k_phi(const S* __restrict__ g, typenam
 // their six neighbours from there.
 // ---------------------------------------------------------------------------
 
-// TRT: the parts of f - f^eq even and odd under c -> -c relax with omega_f
-// and omega_m.  MRT: TRT for the shear stresses (even) and the energy fluxes
-// (odd), and seven more moments of the orthogonal basis with their own rates
-// -- the energy e (omega_b), the even ghosts eps, pi_xx, pi_ww (omega_ge) and
-// the odd ghosts m_x, m_y, m_z (omega_go) -- applied as a correction
-// (omega_k - its TRT rate) times the moment's projection.  neq = f - f^eq.
-template <class P, int COLL, class S, class T>
-__device__ __forceinline__ void relax_moments_store(const T (&f)[Q], const T (&neq)[Q], S* fdst, uint32_t off,
-                                                    int64_t ds, const CollParams<T>& cp) {
-    T a[7] = {T(0), T(0), T(0), T(0), T(0), T(0), T(0)};
-    if constexpr (COLL == COLL_MRT) {
-        static_for<0, 7>([&](auto K) {
-            constexpr int k = decltype(K)::value;
-            constexpr int m = mrt_extra(k);
-            T acc = T(0);
-            static_for<0, Q>([&](auto I) {
-                constexpr int i = decltype(I)::value;
-                constexpr int c = mrt_poly(m, i);
-                if constexpr (c != 0) acc = acc + T(c) * neq[i];
-            });
-            // k = 0: e (bulk); 1-3: eps, pi_xx, pi_ww (even ghosts); 4-6: m (odd ghosts)
-            const T dw = k == 0 ? cp.omega_b - cp.omega_f : (k < 4 ? cp.omega_ge - cp.omega_f : cp.omega_go - cp.omega_m);
-            a[k] = dw * acc / T(mrt_norm(m));
-        });
-    }
-    static_for<0, Q>([&](auto I) {
-        constexpr int i = decltype(I)::value;
-        constexpr int o = opp(i);
-        T corr = T(0);
-        if constexpr (COLL == COLL_MRT) {
-            static_for<0, 7>([&](auto K) {
-                constexpr int k = decltype(K)::value;
-                constexpr int c = mrt_poly(mrt_extra(k), i);
-                if constexpr (c != 0) corr = corr + T(c) * a[k];
-            });
-        }
-        const T np = T(0.5) * (neq[i] + neq[o]);
-        const T nm = T(0.5) * (neq[i] - neq[o]);
-        stg<P::nt_store>(fdst + i * ds, off, static_cast<S>(f[i] - cp.omega_f * np - cp.omega_m * nm - corr));
-    });
-}
-
-// Collision of one site of the single fluid, f -> f*.  Every rounding is
-// written out (fma where one is wanted, no contraction left to the compiler),
-// so each kernel that collides a site gives the same bits whatever surrounds
-// the call: a state does not depend on whether its steps ran one or two to a
-// launch, or were recorded.
+// Collision of one site, in every kernel that collides: each rounding is
+// written out (fma where one is wanted, nothing left to contraction), so all
+// of them give the same bits whatever surrounds the call, and a state does
+// not depend on whether its steps ran one or two to a launch, in one kernel
+// or two, or were recorded.
 template <class T>
 __device__ __forceinline__ T fma_(T a, T b, T c) { return __builtin_elementwise_fma(a, b, c); }
 
-// v rounded to the storage type, v itself first pinned in a register.  For
-// binary16, an fma whose result is only ever stored may otherwise become one
-// mixed-precision instruction that rounds once, and which of them do differs
-// from kernel to kernel; and where a store is conditional the value is
-// otherwise formed again behind each condition (25 VGPRs spilled in the
-// FP32 MRT pair kernel without the pin, none with it).
+// v rounded to the storage type; stored_fma: a b + c rounded to it, which for
+// binary16 is one mixed-precision instruction.  The rounded value is pinned
+// in a register, so it is formed once, here: where a use is conditional the
+// compiler otherwise forms it again behind each condition (25 VGPRs spilled in
+// the FP32 MRT pair kernel without the pin, none with it), and for binary16
+// then as two instructions in some kernels, whose bits differ.
 template <class S, class T>
 __device__ __forceinline__ S stored(T v) {
-    asm("" : "+v"(v));
-    return static_cast<S>(v);
+    S r = static_cast<S>(v);
+    asm("" : "+v"(r));
+    return r;
+}
+template <class S, class T>
+__device__ __forceinline__ S stored_fma(T a, T b, T c) { return stored<S>(fma_(a, b, c)); }
+
+// v . c_I for a moving direction; opposite directions give exact negatives.
+template <int I, class T>
+__device__ __forceinline__ T along(T x, T y, T z) {
+    if constexpr (opp(I) < I) return -along<opp(I)>(x, y, z);
+    else if constexpr (cx(I) != 0 && cy(I) != 0) return cx(I) == cy(I) ? -(x + y) : y - x;
+    else if constexpr (cx(I) != 0 && cz(I) != 0) return cx(I) == cz(I) ? -(x + z) : z - x;
+    else if constexpr (cy(I) != 0 && cz(I) != 0) return cy(I) == cz(I) ? -(y + z) : z - y;
+    else return cx(I) != 0 ? -x : (cy(I) != 0 ? -y : -z);
 }
 
-template <int COLL, class S, class T>
-__device__ __forceinline__ void collide_single(const T (&f)[Q], T (&out)[Q], const CollParams<T>& cp) {
+// Calls fn(i, opp(i)) for the nine pairs of opposite directions.
+template <class F>
+__device__ __forceinline__ void for_pairs(F&& fn) {
+    static_for<1, Q>([&](auto I) {
+        constexpr int i = decltype(I)::value;
+        if constexpr (i < opp(i)) fn(I, std::integral_constant<int, opp(i)>{});
+    });
+}
+
+// TRT and MRT: f - Omega neq, neq = f - f^eq, each direction to put(i, f*_i).
+// The parts even and odd under c -> -c relax with omega_f and omega_m; MRT
+// adds, for each of the seven moments of the orthogonal basis with a rate of
+// their own -- the energy e (omega_b), the even ghosts eps, pi_xx, pi_ww
+// (omega_ge) and the odd ghosts m_x, m_y, m_z (omega_go) -- (omega_k - its
+// TRT rate) times the moment's projection.
+template <int COLL, class S, class T, class F>
+__device__ __forceinline__ void relax_parts(const T (&f)[Q], const T (&neq)[Q], const CollParams<T>& cp, F&& put) {
+#pragma clang fp contract(off)
+    T a[7] = {T(0), T(0), T(0), T(0), T(0), T(0), T(0)};
+    if constexpr (COLL == COLL_MRT) {
+        static_for<0, 7>([&](auto K) {
+#pragma clang fp contract(off)
+            constexpr int k = decltype(K)::value;
+            T acc = T(0);
+            static_for<0, Q>([&](auto I) {
+                constexpr int i = decltype(I)::value;
+                constexpr int c = mrt_poly(mrt_extra(k), i);
+                if constexpr (c != 0) acc = fma_(T(c), neq[i], acc);
+            });
+            // k = 0: e (bulk); 1-3: eps, pi_xx, pi_ww (even ghosts); 4-6: m (odd ghosts)
+            const T dw = k == 0 ? cp.omega_b - cp.omega_f : (k < 4 ? cp.omega_ge - cp.omega_f : cp.omega_go - cp.omega_m);
+            a[k] = dw * acc / T(mrt_norm(mrt_extra(k)));
+        });
+    }
+    static_for<0, Q>([&](auto I) {
+#pragma clang fp contract(off)
+        constexpr int i = decltype(I)::value;
+        constexpr int o = opp(i);
+        const T even = fma_(-cp.omega_f, T(0.5) * (neq[i] + neq[o]), f[i]);
+        const T nm = T(0.5) * (neq[i] - neq[o]);
+        if constexpr (COLL == COLL_MRT) {
+            T corr = T(0);
+            static_for<0, 7>([&](auto K) {
+                constexpr int k = decltype(K)::value;
+                constexpr int c = mrt_poly(mrt_extra(k), i);
+                if constexpr (c != 0) corr = fma_(T(c), a[k], corr);
+            });
+            put(I, stored<S>(fma_(-cp.omega_m, nm, even) - corr));
+        } else {
+            put(I, stored_fma<S>(-cp.omega_m, nm, even));
+        }
+    });
+}
+
+// Single fluid: put(i, f*_i) receives every direction once, rounded to S.
+template <int COLL, class S, class T, class F>
+__device__ __forceinline__ void collide_single(const T (&f)[Q], const CollParams<T>& cp, F&& put) {
 #pragma clang fp contract(off)
     T drho, jx, jy, jz;
     moments_in<typename Accum<S>::T>(f, drho, jx, jy, jz);
     const T rho = cp.rho0 + drho;
     const T ux = jx / rho, uy = jy / rho, uz = jz / rho;
-    const T usq = T(-1.5) * fma_(uz, uz, fma_(uy, uy, ux * ux));
-    const auto neq_of = [&](auto I) {
-#pragma clang fp contract(off)
+    const T usq = fma_(uz, uz, fma_(ux, ux, uy * uy));
+    T neq[Q];
+    auto one = [&](auto I, T base) {       // base = f^eq / (w rho) - 1
         constexpr int i = decltype(I)::value;
-        const T cu = cdot<i>(ux, uy, uz);
-        const T base = fma_(T(3), cu, fma_(T(4.5) * cu, cu, usq));
-        return fma_(-weight<T>(i), fma_(rho, base, drho), f[i]);
+        const T n = fma_(-weight<T>(i), fma_(rho, base, drho), f[i]);
+        if constexpr (COLL == COLL_BGK) put(I, stored_fma<S>(-cp.omega_f, n, f[i]));
+        else neq[i] = n;
     };
-    if constexpr (COLL == COLL_BGK) {
-        static_for<0, Q>([&](auto I) {
-            constexpr int i = decltype(I)::value;
-            out[i] = fma_(-cp.omega_f, neq_of(I), f[i]);
-        });
-    } else {
-        T neq[Q];
-        static_for<0, Q>([&](auto I) { neq[decltype(I)::value] = neq_of(I); });
-        T a[7] = {T(0), T(0), T(0), T(0), T(0), T(0), T(0)};
-        if constexpr (COLL == COLL_MRT) {
-            static_for<0, 7>([&](auto K) {
+    one(std::integral_constant<int, 0>{}, T(-1.5) * usq);
+    for_pairs([&](auto I, auto O) {
 #pragma clang fp contract(off)
-                constexpr int k = decltype(K)::value;
-                T acc = T(0);
-                static_for<0, Q>([&](auto I) {
-                    constexpr int i = decltype(I)::value;
-                    constexpr int c = mrt_poly(mrt_extra(k), i);
-                    if constexpr (c != 0) acc = fma_(T(c), neq[i], acc);
-                });
-                // k = 0: energy (bulk); 1-3: eps, pi_xx, pi_ww (even ghosts); 4-6: m (odd ghosts)
-                const T dw = k == 0 ? cp.omega_b - cp.omega_f : (k < 4 ? cp.omega_ge - cp.omega_f : cp.omega_go - cp.omega_m);
-                a[k] = dw * (T(1) / T(mrt_norm(mrt_extra(k)))) * acc;
-            });
-        }
-        static_for<0, Q>([&](auto I) {
-#pragma clang fp contract(off)
-            constexpr int i = decltype(I)::value;
-            constexpr int o = opp(i);
-            T r = fma_(cp.omega_f, T(0.5) * (neq[i] + neq[o]), cp.omega_m * (T(0.5) * (neq[i] - neq[o])));
-            if constexpr (COLL == COLL_MRT) {
-                static_for<0, 7>([&](auto K) {
-                    constexpr int k = decltype(K)::value;
-                    constexpr int c = mrt_poly(mrt_extra(k), i);
-                    if constexpr (c != 0) r = fma_(T(c), a[k], r);
-                });
-            }
-            out[i] = f[i] - r;
-        });
-    }
+        const T cu = along<decltype(I)::value>(ux, uy, uz);
+        const T m = cu * (T(4.5) * cu);
+        one(I, fma_(T(-1.5), usq, fma_(T(3), cu, m)));
+        one(O, fma_(T(-1.5), usq, fma_(T(-3), cu, m)));
+    });
+    if constexpr (COLL != COLL_BGK) relax_parts<COLL, S>(f, neq, cp, put);
 }
 
 // collide_single, stored: every post-collision value before the first store
@@ -287,49 +283,68 @@ __device__ __forceinline__ void collide_single(const T (&f)[Q], T (&out)[Q], con
 template <class P, int COLL = COLL_BGK, class S, class T>
 __device__ __forceinline__ void relax_single(const T (&f)[Q], S* fdst, uint32_t off, const Geo& geo,
                                              const CollParams<T>& cp) {
-    T out[Q];
-    collide_single<COLL, S>(f, out, cp);
+    S out[Q];
+    collide_single<COLL, S>(f, cp, [&](auto I, S v) { out[decltype(I)::value] = v; });
     static_for<0, Q>([&](auto I) {
         constexpr int i = decltype(I)::value;
-        stg<P::nt_store>(fdst + i * geo.dstride, off, stored<S>(out[i]));
+        stg<P::nt_store>(fdst + i * geo.dstride, off, out[i]);
     });
 }
 
-// Binary collision of one site: g relaxes with omega_g (BGK); f with BGK, or
-// with TRT / MRT around the same f^eq (relax_moments_store).
-template <class P, int COLL = COLL_BGK, class S, class T>
-__device__ __forceinline__ void relax_binary(const T (&f)[Q], const T (&g)[Q], S* fdst, S* gdst, uint32_t off,
-                                             const Geo& geo, const CollParams<T>& cp, T phic, T gx, T gy, T gz,
-                                             T lap) {
+// Central differences and the 7-point Laplacian of phi, from the six
+// neighbours and the site itself.
+template <class T>
+struct Stencil {
+    T phi, gx, gy, gz, lap;
+    __device__ __forceinline__ Stencil(T c, T xm, T xp, T ym, T yp, T zm, T zp)
+        : phi(c), gx(T(0.5) * (xp - xm)), gy(T(0.5) * (yp - ym)), gz(T(0.5) * (zp - zm)),
+          lap(fma_(T(-6), c, ((xp + xm) + (yp + ym)) + (zp + zm))) {}
+};
+
+// Binary fluid: g relaxes with omega_g (BGK), f by any collision;
+// put_f(i, f*_i) and put_g(i, g*_i) receive every direction once, rounded to S.
+template <int COLL, class S, class T, class F, class G>
+__device__ __forceinline__ void collide_binary(const T (&f)[Q], const T (&g)[Q], const CollParams<T>& cp,
+                                               const Stencil<T>& st, F&& put_f, G&& put_g) {
+#pragma clang fp contract(off)
+    const T phi = st.phi, lap = st.lap;
     T drho, jx, jy, jz;
     moments_in<typename Accum<S>::T>(f, drho, jx, jy, jz);
     const T rho = cp.rho0 + drho;
     const T ux = jx / rho, uy = jy / rho, uz = jz / rho;
-    const T usq = ux * ux + uy * uy + uz * uz;
-    const FreeEnergy<T> fe(phic, gx, gy, gz, lap, cp);
-    const T dphi = phic - cp.phi0;
-    if constexpr (COLL != COLL_BGK) {
-        T neq[Q];
-        static_for<0, Q>([&](auto I) {
-            constexpr int i = decltype(I)::value;
-            const T cu = cdot<i>(ux, uy, uz);
-            const T base = T(3) * cu + T(4.5) * cu * cu - T(1.5) * usq;
-            neq[i] = f[i] - weight<T>(i) * (drho + rho * base + fe.template stress_term<i>(cp));
-            const T geq = weight<T>(i) * (dphi + phic * base + fe.template mobility_term<i>(cp));
-            stg<P::nt_store>(gdst + i * geo.dstride, off, static_cast<S>(g[i] - cp.omega_g * (g[i] - geq)));
-        });
-        relax_moments_store<P, COLL>(f, neq, fdst, off, geo.dstride, cp);
-        return;
-    }
-    static_for<0, Q>([&](auto I) {
+    const T usq = fma_(uz, uz, fma_(ux, ux, uy * uy));
+    // chemical potential, and the parts of the stress (see FreeEnergy)
+    const T phi2 = phi * phi;
+    const T gsq = fma_(st.gz, st.gz, fma_(st.gx, st.gx, st.gy * st.gy));
+    const T mu = fma_(-cp.kappa, lap, fma_(cp.A, phi, phi * (cp.B * phi2)));
+    const T iso = fma_(-(T(0.5) * cp.kappa), gsq,
+                       fma_(-(cp.kappa * phi), lap, fma_(T(0.5) * cp.A, phi2, phi2 * (T(0.75) * cp.B * phi2))));
+    const T k3 = cp.kappa * gsq / T(3);
+    const T mob = fma_(cp.gamma, mu, -(phi / T(3)));
+    const T dphi = phi - cp.phi0;
+    T neq[Q];
+    auto one = [&](auto I, T base, T stress) {
         constexpr int i = decltype(I)::value;
-        const T cu = cdot<i>(ux, uy, uz);
-        const T base = T(3) * cu + T(4.5) * cu * cu - T(1.5) * usq;
-        const T feq = weight<T>(i) * (drho + rho * base + fe.template stress_term<i>(cp));
-        const T geq = weight<T>(i) * (dphi + phic * base + fe.template mobility_term<i>(cp));
-        stg<P::nt_store>(fdst + i * geo.dstride, off, static_cast<S>(f[i] - cp.omega_f * (f[i] - feq)));
-        stg<P::nt_store>(gdst + i * geo.dstride, off, static_cast<S>(g[i] - cp.omega_g * (g[i] - geq)));
+        const T n = fma_(-weight<T>(i), fma_(T(4.5), stress, fma_(rho, base, drho)), f[i]);
+        T ge = fma_(base, phi, dphi);
+        if constexpr (csq(i) != 1) ge = fma_(T(csq(i) == 0 ? -4.5 : 4.5), mob, ge);
+        const T m = fma_(-weight<T>(i), ge, g[i]);
+        if constexpr (COLL == COLL_BGK) put_f(I, stored_fma<S>(-cp.omega_f, n, f[i]));
+        else neq[i] = n;
+        put_g(I, stored_fma<S>(-cp.omega_g, m, g[i]));
+    };
+    one(std::integral_constant<int, 0>{}, T(-1.5) * usq, -iso - k3);
+    for_pairs([&](auto I, auto O) {
+#pragma clang fp contract(off)
+        constexpr int i = decltype(I)::value;
+        const T cu = along<i>(ux, uy, uz);
+        const T cg = along<i>(st.gx, st.gy, st.gz);
+        const T m = cu * (T(4.5) * cu);
+        const T stress = csq(i) == 1 ? fma_(cg, cp.kappa * cg, -k3) : fma_(cg, cp.kappa * cg, iso) - k3;
+        one(I, fma_(T(-1.5), usq, fma_(T(3), cu, m)), stress);
+        one(O, fma_(T(-1.5), usq, fma_(T(-3), cu, m)), stress);
     });
+    if constexpr (COLL != COLL_BGK) relax_parts<COLL, S>(f, neq, cp, put_f);
 }
 
 template <class P, int MODEL, class S, bool GATHER, int COLL = COLL_BGK>
@@ -363,14 +378,15 @@ __global__ __launch_bounds__(P::TPB) void k_collide(const S* fsrc, const S* gsrc
             const T pxm = tile[lz][ly][lx - 1], pxp = tile[lz][ly][lx + 1];
             const T pym = tile[lz][ly - 1][lx], pyp = tile[lz][ly + 1][lx];
             const T pzm = tile[lz - 1][ly][lx], pzp = tile[lz + 1][ly][lx];
-            const T gx = T(0.5) * (pxp - pxm);
-            const T gy = T(0.5) * (pyp - pym);
-            const T gz = T(0.5) * (pzp - pzm);
-            const T lap = (pxp + pxm) + (pyp + pym) + (pzp + pzm) - T(6) * phic;
+            const Stencil<T> sten(phic, pxm, pxp, pym, pyp, pzm, pzp);
             T f[Q], g[Q];
             load_site<P, GATHER>(fsrc, st, geo, f);
             load_site<P, GATHER>(gsrc, st, geo, g);
-            relax_binary<P, COLL>(f, g, fdst, gdst, offset_at<0, 0, 0>(st, geo), geo, cp, phic, gx, gy, gz, lap);
+            const uint32_t off = offset_at<0, 0, 0>(st, geo);
+            collide_binary<COLL, S>(
+                f, g, cp, sten,
+                [&](auto I, S v) { stg<P::nt_store>(fdst + decltype(I)::value * geo.dstride, off, v); },
+                [&](auto I, S v) { stg<P::nt_store>(gdst + decltype(I)::value * geo.dstride, off, v); });
         }
     } else {
 #pragma unroll
@@ -404,17 +420,15 @@ __global__ __launch_bounds__(P::TPB) void k_collide_single_strided(const S* fsrc
 
 // ---------------------------------------------------------------------------
 // Single-pass binary step: fused pull-stream + collision that computes phi
-// itself.  A block owns a TX x TY column tile and marches through one chunk
-// of at most geo.bz consecutive z planes (geo.gz chunks).  phi(s) = phi0 + sum_i e_i(s - c_i) needs the pulled
+// itself.  A block owns a TX x TY column tile and marches through one of
+// geo.gz chunks of z planes.  phi(s) = phi0 + sum_i e_i(s - c_i) needs the pulled
 // g of s, which the collision of s needs anyway: each lane gathers g for
 // plane z+1, sums it into the plane's phi tile in LDS and keeps the 19 values
-// for the next plane's collision, in registers or (GLDS) in LDS.  On small
-// lattices the host picks the two-pass step instead, because a few blocks
-// walking their planes in sequence cannot hide the per-plane latency.
+// for the next plane's collision, in registers or (GLDS) in LDS.
 // The x/y halo ring of the
 // tile (2 TX + 2 TY sites per plane) is summed by one lane each from its own
 // gather; the chunk's first and last plane need one extra plane of phi each.
-// Three phi planes (z-1, z, z+1) rotate in LDS.  Lanes outside the lattice
+// The phi planes rotate in LDS.  Lanes outside the lattice
 // (ragged tiles) compute phi at the periodic image of their coordinates so
 // that every LDS slot holds the value its neighbours read.  The summation
 // order of phi is the same as in k_phi, so results equal the two-pass path.
@@ -438,147 +452,222 @@ __device__ __forceinline__ int wrap_plane(int z, int nz) {
     return z < 0 ? z + nz : (z >= nz ? z - nz : z);
 }
 
-// phi of the pulled g at st: the 19 values are loaded into registers first
-// and then summed (in k_phi's order), so the loads go out as one batch
-// rather than one at a time behind the running sum.
-template <class P, class S, class T>
-__device__ __forceinline__ T phi_of_gathered(const S* g, const Site& st, const Geo& geo, T phi0) {
+// Addresses of a marching block.  Everything that depends on the plane is the
+// same for the whole block, so it goes into scalar registers: one base per
+// plane and 4 KiB of the blocked layout's 19 directions (the reach of a
+// load's immediate offset); what is left to a lane is the 32-bit offset of
+// its nine (x, y) neighbours, formed once.  A pull is then a single
+// instruction with no vector arithmetic, and only a plane, not a buffer, has
+// to stay below 4 GiB.  The empty asm statements keep the compiler from
+// moving parts of the sum back into per-lane 64-bit registers (FP32 march:
+// 123 VGPRs with them, 137 before).
+#define LB_GLOBAL __attribute__((address_space(1)))
+
+// Byte offsets of (x, y) and its neighbours in a plane, element 3 (dy + 1) + dx + 1.
+struct InPlane { uint32_t at[9]; };
+
+template <class S>
+__device__ __forceinline__ InPlane in_plane(int x, int y, const Geo& g) {
+    const uint32_t xs[3] = {(uint32_t)(x == 0 ? g.nx - 1 : x - 1), (uint32_t)x, (uint32_t)(x + 1 >= g.nx ? 0 : x + 1)};
+    const uint32_t ys[3] = {(uint32_t)(y == 0 ? g.ny - 1 : y - 1), (uint32_t)y, (uint32_t)(y + 1 >= g.ny ? 0 : y + 1)};
+    InPlane r;
+#pragma unroll
+    for (int k = 0; k < 9; ++k)
+        r.at[k] = (ys[k / 3] * g.ys + (xs[k % 3] >> 6) * g.xbs + (xs[k % 3] & 63u)) * (uint32_t)sizeof(S);
+    return r;
+}
+
+// Plane z of a distribution: direction i of the element at byte offset o.
+template <class S, bool BLK>
+struct PlaneBase {
+    static constexpr int N = BLK ? (Q * 64 * (int)sizeof(S) + 4095) / 4096 : 1;
+    const LB_GLOBAL char* p[N];
+    int64_t stride;                       // bytes between directions (not blocked)
+    __device__ __forceinline__ PlaneBase(const S* base, int z, const Geo& g) : stride(g.dstride * (int64_t)sizeof(S)) {
+        const LB_GLOBAL char* b = (const LB_GLOBAL char*)base +
+                                  (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane(z) * g.zs * sizeof(S);
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            p[k] = b + 4096 * k;
+            asm("" : "+s"(p[k]));
+        }
+    }
+    template <int I>
+    __device__ __forceinline__ const LB_GLOBAL S* dir(uint32_t o) const {
+        constexpr int by = I * 64 * (int)sizeof(S);
+        if constexpr (BLK) return (const LB_GLOBAL S*)(p[by / 4096] + o + by % 4096);
+        else return (const LB_GLOBAL S*)(p[0] + I * stride + o);
+    }
+};
+
+// The 19 values of the site (x, y, z) in the storage type: pulled (GATHER)
+// from a pending distribution, or its own of a direct one.
+template <class P, class S, bool BLK, bool GATHER = true>
+__device__ __forceinline__ void pull_plane(const S* src, int z, const Geo& g, InPlane ip, S (&v)[Q]) {
+    const PlaneBase<S, BLK> pl[3] = {PlaneBase<S, BLK>(src, z == 0 ? g.nz - 1 : z - 1, g),
+                                     PlaneBase<S, BLK>(src, z, g),
+                                     PlaneBase<S, BLK>(src, z + 1 >= g.nz ? 0 : z + 1, g)};
+#pragma unroll
+    for (int k = 0; k < 9; ++k) asm volatile("" : "+v"(ip.at[k]));
+    static_for<0, Q>([&](auto I) {
+        constexpr int i = decltype(I)::value;
+        const LB_GLOBAL S* q = GATHER ? pl[1 - cz(i)].template dir<i>(ip.at[3 * (1 - cy(i)) + (1 - cx(i))])
+                                      : pl[1].template dir<i>(ip.at[4]);
+        v[i] = P::nt_load ? __builtin_nontemporal_load(q) : *q;
+    });
+}
+
+// Stores of a marching kernel: nontemporal or not, by the policy.
+template <class P, class S>
+__device__ __forceinline__ void put_at(const LB_GLOBAL S* p, S v) {
+    if constexpr (P::nt_store) __builtin_nontemporal_store(v, (LB_GLOBAL S*)p);
+    else *(LB_GLOBAL S*)p = v;
+}
+
+// phi of 19 values of g in the storage type, summed in k_phi's order.
+template <class S, class T>
+__device__ __forceinline__ T phi_stored(const S (&e)[Q], T phi0) {
     T v[Q];
-    load_site<P, true>(g, st, geo, v);
+#pragma unroll
+    for (int i = 0; i < Q; ++i) v[i] = static_cast<T>(e[i]);
     return phi_sum<typename Accum<S>::T>(v, phi0);
 }
 
-// With GLDS the 19 pulled g of the next plane wait in LDS (each lane only
-// touches its own slots, so no barrier is involved) instead of registers,
-// which lowers register pressure and raises occupancy.  RING is the number of
-// phi planes kept in LDS: with 3 a second barrier per plane keeps the write of
-// plane z+2 from overtaking the reads of plane z-1; with 4 the slot written
-// next is never one still being read, so one barrier per plane suffices.
+// How the march holds its values, per storage type and tile.
+//   early:      the next plane's f and g are loaded before this plane's
+//               collision, whose arithmetic and stores cover their latency (a
+//               load issued after the stores would also wait for them).  In
+//               FP16 only with 64 x 8 tiles: 160^3 173 against 183 us, 192^3
+//               237 against 253; with 128 x 4 ones, whose ring is another 264
+//               gathers, it costs 1% at 384^3.
+//   early_halo: the ring's g too (FP32, template flag HALO).
+//   in_lds:     the next plane's g waits in LDS (each lane only touches its own
+//               slots, so no barrier is involved) instead of in registers:
+//               in FP64 a plane's f and g and the next one's are 304 VGPRs.
+//   planes:     phi planes in LDS.  With 3 a second barrier per plane would
+//               keep the write of plane z+2 from overtaking the reads of plane
+//               z-1 (3-6% slower in FP32 and FP16); with 4 the slot written
+//               next is never one still being read.
+//   waves:      per SIMD, which sets how many 512-lane blocks a CU holds.
+// FP64 256^3: 1816 us a step early, 1850 not; FP32 256^3 897, 986 not early
+// at four waves; FP16 256^3 543.
+template <class S, int TX, bool HALO>
+struct MarchHold {
+    static constexpr bool early = sizeof(S) > 2 || TX == 64, early_halo = early && HALO, in_lds = sizeof(S) != 4;
+    static constexpr int planes = 4, waves = sizeof(S) == 2 ? 4 : 2;
+};
+
 // With PHI_OUT the kernel also stores the phi it computes for its own sites
 // (phi_out[s], canonical), i.e. phi of the state this step collides.
-// BLK: the arrays are in the blocked layout, whose direction stride (64
-// elements) is then a compile-time constant: every direction of a site is
-// one address plus an immediate offset, and a site's loads need one 64-bit
-// address instead of one per direction.
-template <class P, class S, bool GLDS, int RING = 3, bool PHI_OUT = false, int COLL = COLL_BGK, bool BLK = false>
-__global__ __launch_bounds__(P::TPB) void k_binary_march(const S* __restrict__ fsrc, const S* __restrict__ gsrc,
-                                                         S* __restrict__ fdst, S* __restrict__ gdst, Geo geo_in,
-                                                         CollParams<typename Compute<S>::T> cp,
-                                                         typename Compute<S>::T* __restrict__ phi_out = nullptr) {
+// BLK: the arrays are in the blocked layout.
+template <class P, class S, bool PHI_OUT, int COLL, bool BLK, bool HALO>
+__global__ __launch_bounds__(P::TPB, (MarchHold<S, P::TX, HALO>::waves)) void k_binary_march(
+    const S* __restrict__ fsrc, const S* __restrict__ gsrc, S* __restrict__ fdst, S* __restrict__ gdst, Geo geo,
+    CollParams<typename Compute<S>::T> cp, typename Compute<S>::T* __restrict__ phi_out) {
     using T = typename Compute<S>::T;
-    Geo geo = geo_in;
-    if constexpr (BLK) geo.dstride = 64;
-    constexpr int TX = P::TX, TY = P::TY, LX = TX + 2, LY = TY + 2;
-    constexpr int NHALO = 2 * TX + 2 * TY;
-    static_assert(NHALO <= P::TPB, "one halo site per lane");
-    static_assert(RING == 3 || RING == 4, "3 or 4 phi planes");
-    __shared__ T ring[RING][LY][LX];
-    __shared__ T gkeep[GLDS ? Q : 1][GLDS ? P::TPB : 1];
+    using H = MarchHold<S, P::TX, HALO>;
+    constexpr int TX = P::TX, TY = P::TY, LX = TX + 2, RING = H::planes;
+    static_assert(2 * TX + 2 * TY <= P::TPB, "one halo site per lane");
+    __shared__ T ring[RING][(TY + 2) * LX];
+    __shared__ S gkeep[H::in_lds ? Q : 1][H::in_lds ? P::TPB : 1];
 
-    const int b = tile_index<P>(geo);
-    const int bx = b % geo.gx;
-    const int t = b / geo.gx;
-    const int by = t % geo.gy;
-    // Under the XCD remap each XCD takes a contiguous run of tiles, so a short
-    // last chunk would land on the last XCDs and leave them idle while the
-    // others finish: the gz chunks then split nz evenly (8-14% faster at 208^3
-    // with 64-plane chunks).  Without the remap blocks reach the XCDs in launch
-    // order and the short last chunk, launched last, fills the tail (even
-    // chunks measured 5-6% slower at 272^3).
-    const int zc = t / geo.gy;
-    int z0, z1;
-    if (xcd_remapped<P>(geo)) {
-        z0 = (int)((int64_t)zc * geo.nz / geo.gz);
-        z1 = (int)((int64_t)(zc + 1) * geo.nz / geo.gz);
-    } else {
-        z0 = zc * geo.bz;
-        z1 = min(z0 + geo.bz, geo.nz);
-    }
-    const int x0 = bx * TX, y0 = by * TY;
-    const int tx = (int)(threadIdx.x % TX), ty = (int)(threadIdx.x / TX);
-    const bool active = (x0 + tx < geo.nx) && (y0 + ty < geo.ny);
-    const int xw = (x0 + tx) % geo.nx, yw = (y0 + ty) % geo.ny;
+    TileAt tile;
+    if (!tile_of_block<P>(geo, tile)) return;
+    const int z0 = tile.z0, z1 = tile.z1;
+    const int k = threadIdx.x, tx = k % TX, ty = k / TX;
+    const bool active = (tile.x0 + tx < geo.nx) && (tile.y0 + ty < geo.ny);
+    const int x = image_of(tile.x0 + tx, geo.nx), y = image_of(tile.y0 + ty, geo.ny);
+    // this lane's site of the ring around the tile, if any
+    int rx, ry;
+    const bool has_halo = ring_site<P, false>(k, rx, ry);
+    const InPlane own = in_plane<S>(x, y, geo),
+                  halo = in_plane<S>(image_of(tile.x0 + rx, geo.nx), image_of(tile.y0 + ry, geo.ny), geo);
+    const uint32_t site = (uint32_t)y * (uint32_t)geo.nx + (uint32_t)x;      // in a canonical plane
+    const int me = (ty + 1) * LX + tx + 1, at_halo = (ry + 1) * LX + rx + 1;  // LDS slots
 
-    // This lane's halo site (if any): LDS slot (hlx, hly) of the ring, taken
-    // in order (the y-halo rows land on whole wavefronts, so their gathers are
-    // contiguous; measured faster than spreading the ring over all
-    // wavefronts).
-    const int k = threadIdx.x;
-    int hlx = 0, hly = 0;
-    if (k < TX) { hlx = k + 1; hly = 0; }
-    else if (k < 2 * TX) { hlx = k - TX + 1; hly = TY + 1; }
-    else if (k < 2 * TX + TY) { hlx = 0; hly = k - 2 * TX + 1; }
-    else if (k < NHALO) { hlx = TX + 1; hly = k - 2 * TX - TY + 1; }
-    const bool has_halo = k < NHALO;
-    int hx = (x0 - 1 + hlx) % geo.nx, hy = (y0 - 1 + hly) % geo.ny;
-    hx += hx < 0 ? geo.nx : 0;
-    hy += hy < 0 ? geo.ny : 0;
-
-    const int lx = tx + 1, ly = ty + 1;
     auto slot = [&](int z) { return (z - z0 + RING) % RING; };
+    auto pull = [&](const S* src, int z, const InPlane& ip, S (&v)[Q]) { pull_plane<P, S, BLK>(src, z, geo, ip, v); };
 
     // Prologue: phi of planes z0-1 and z0; g of plane z0 kept for its collision.
-    T gc[Q];
+    S gc[Q], fn[Q], gn[Q], hn[Q];
     {
         const int zm = wrap_plane(z0 - 1, geo.nz);
-        ring[slot(z0 - 1)][ly][lx] = phi_of_gathered<P>(gsrc, site_wrapped(xw, yw, zm, geo), geo, cp.phi0);
-        if (has_halo)
-            ring[slot(z0 - 1)][hly][hlx] = phi_of_gathered<P>(gsrc, site_wrapped(hx, hy, zm, geo), geo, cp.phi0);
-        const Site s0 = site_wrapped(xw, yw, z0, geo);
-        load_site<P, true>(gsrc, s0, geo, gc);
-        ring[slot(z0)][ly][lx] = phi_sum<typename Accum<S>::T>(gc, cp.phi0);
-        if constexpr (PHI_OUT)
-            if (active) phi_out[canon_at<0, 0, 0>(s0, geo)] = ring[slot(z0)][ly][lx];
-        if constexpr (GLDS) {
-#pragma unroll
-            for (int i = 0; i < Q; ++i) gkeep[i][threadIdx.x] = gc[i];
+        S v[Q];
+        pull(gsrc, zm, own, v);
+        pull(gsrc, z0, own, gc);
+        if constexpr (H::early) {
+            pull(fsrc, z0, own, fn);
+            pull(gsrc, wrap_plane(z0 + 1, geo.nz), own, gn);
+            if constexpr (H::early_halo)
+                if (has_halo) pull(gsrc, wrap_plane(z0 + 1, geo.nz), halo, hn);
         }
-        if (has_halo)
-            ring[slot(z0)][hly][hlx] = phi_of_gathered<P>(gsrc, site_wrapped(hx, hy, z0, geo), geo, cp.phi0);
+        ring[slot(z0 - 1)][me] = phi_stored(v, cp.phi0);
+        const T p0 = phi_stored(gc, cp.phi0);
+        ring[slot(z0)][me] = p0;
+        if constexpr (PHI_OUT)
+            if (active) phi_out[(uint32_t)z0 * geo.plane + site] = p0;
+        if (has_halo) {
+            S h[Q];
+            pull(gsrc, zm, halo, v);
+            pull(gsrc, z0, halo, h);
+            ring[slot(z0 - 1)][at_halo] = phi_stored(v, cp.phi0);
+            ring[slot(z0)][at_halo] = phi_stored(h, cp.phi0);
+        }
+        if constexpr (H::in_lds) {
+#pragma unroll
+            for (int i = 0; i < Q; ++i) gkeep[i][k] = gc[i];
+        }
     }
 
     for (int z = z0; z < z1; ++z) {
         const int zn = wrap_plane(z + 1, geo.nz);
-        const Site sc = site_wrapped(xw, yw, z, geo);
-        // every lane loads (a lane outside a ragged tile reads the periodic
-        // image of its coordinates, valid memory it never stores), so these
-        // loads share one basic block, and one wait, with the g loads below
-        T fc[Q];
-        load_site<P, true>(fsrc, sc, geo, fc);
-        T gn[Q];
-        load_site<P, true>(gsrc, site_wrapped(xw, yw, zn, geo), geo, gn);
-        ring[slot(z + 1)][ly][lx] = phi_sum<typename Accum<S>::T>(gn, cp.phi0);
+        if constexpr (!H::early) {
+            pull(fsrc, z, own, fn);
+            pull(gsrc, zn, own, gn);
+        }
+        const T pn = phi_stored(gn, cp.phi0);
+        ring[slot(z + 1)][me] = pn;
         if constexpr (PHI_OUT)
-            if (active && z + 1 < z1) phi_out[canon_at<0, 0, 0>(site_wrapped(xw, yw, zn, geo), geo)] =
-                ring[slot(z + 1)][ly][lx];
-        if (has_halo)
-            ring[slot(z + 1)][hly][hlx] = phi_of_gathered<P>(gsrc, site_wrapped(hx, hy, zn, geo), geo, cp.phi0);
-        if constexpr (GLDS) {
-            // swap this plane's g out of LDS and park the next plane's
+            if (active && z + 1 < z1) phi_out[(uint32_t)zn * geo.plane + site] = pn;
+        if (has_halo) {
+            if constexpr (!H::early_halo) pull(gsrc, zn, halo, hn);
+            ring[slot(z + 1)][at_halo] = phi_stored(hn, cp.phi0);
+        }
+        T f[Q], g[Q];
 #pragma unroll
-            for (int i = 0; i < Q; ++i) {
-                gc[i] = gkeep[i][threadIdx.x];
-                gkeep[i][threadIdx.x] = gn[i];
+        for (int i = 0; i < Q; ++i) {
+            if constexpr (H::in_lds) {       // this plane's g out of LDS, the next plane's in
+                gc[i] = gkeep[i][k];
+                gkeep[i][k] = gn[i];
             }
+            f[i] = static_cast<T>(fn[i]);
+            g[i] = static_cast<T>(gc[i]);
+            if constexpr (!H::in_lds) gc[i] = gn[i];
         }
         __syncthreads();
+        if constexpr (H::early) {
+            if (z + 1 < z1) {
+                pull(fsrc, zn, own, fn);
+                pull(gsrc, wrap_plane(z + 2, geo.nz), own, gn);
+                if constexpr (H::early_halo)
+                    if (has_halo) pull(gsrc, wrap_plane(z + 2, geo.nz), halo, hn);
+            }
+        }
         if (active) {
             const int r = slot(z);
-            const T phic = ring[r][ly][lx];
-            const T pxm = ring[r][ly][lx - 1], pxp = ring[r][ly][lx + 1];
-            const T pym = ring[r][ly - 1][lx], pyp = ring[r][ly + 1][lx];
-            const T pzm = ring[slot(z - 1)][ly][lx], pzp = ring[slot(z + 1)][ly][lx];
-            const T gx = T(0.5) * (pxp - pxm);
-            const T gy = T(0.5) * (pyp - pym);
-            const T gz = T(0.5) * (pzp - pzm);
-            const T lap = (pxp + pxm) + (pyp + pym) + (pzp + pzm) - T(6) * phic;
-            relax_binary<P, COLL>(fc, gc, fdst, gdst, offset_at<0, 0, 0>(sc, geo), geo, cp, phic, gx, gy, gz, lap);
+            const T phic = ring[r][me];
+            const T pxm = ring[r][me - 1], pxp = ring[r][me + 1];
+            const T pym = ring[r][me - LX], pyp = ring[r][me + LX];
+            const T pzm = ring[slot(z - 1)][me], pzp = ring[slot(z + 1)][me];
+            const Stencil<T> st(phic, pxm, pxp, pym, pyp, pzm, pzp);
+            const PlaneBase<S, BLK> fd(fdst, z, geo), gd(gdst, z, geo);
+            uint32_t off = own.at[4];
+            asm volatile("" : "+v"(off));
+            collide_binary<COLL, S>(
+                f, g, cp, st,
+                [&](auto I, S v) { put_at<P>(fd.template dir<decltype(I)::value>(off), v); },
+                [&](auto I, S v) { put_at<P>(gd.template dir<decltype(I)::value>(off), v); });
         }
-        if constexpr (!GLDS) {
-#pragma unroll
-            for (int i = 0; i < Q; ++i) gc[i] = gn[i];
-        }
-        if constexpr (RING == 3) __syncthreads();
     }
 }
 
@@ -618,43 +707,40 @@ __host__ __device__ constexpr int planar_slot(int i) {
 }
 static_assert(planar_slot(Q) == 16, "directions that leave the column");
 
-template <class P, class S, bool GATHER, int COLL, bool BLK, bool WIDE, bool REC>
+template <class P, class S, bool GATHER, int COLL, bool BLK, bool REC>
 __global__ __launch_bounds__(P::TPB, sizeof(S) == 8 ? 2 : 4) void k_single_pair(
-    const S* __restrict__ src, S* __restrict__ mid, S* __restrict__ dst, Geo geo_in,
+    const S* __restrict__ src, S* __restrict__ mid, S* __restrict__ dst, Geo geo,
     CollParams<typename Compute<S>::T> cp) {
     using T = typename Compute<S>::T;
-    Geo geo = geo_in;
-    if constexpr (BLK) geo.dstride = 64;
-    constexpr int TX = P::TX, TY = P::TY, NRING = 2 * TX + 2 * TY + 4;
-    static_assert(NRING <= P::TPB, "one ring site per lane");
+    constexpr int TX = P::TX, TY = P::TY;
+    static_assert(2 * TX + 2 * TY + 4 <= P::TPB, "one ring site per lane");
     __shared__ S moved[2][16][P::TPB];
 
-    // tiles in XCD order for any count: the grid is rounded up to a multiple
-    // of 8 and the surplus blocks leave at once
-    const int b = (int)((blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3));
-    if (b >= geo.nblocks) return;
-    const int bx = b % geo.gx;
-    const int by = (b / geo.gx) % geo.gy;
-    const int zc = b / (geo.gx * geo.gy);
-    const int z0 = (int)((int64_t)zc * geo.nz / geo.gz), z1 = (int)((int64_t)(zc + 1) * geo.nz / geo.gz);
-    const int x0 = bx * TX, y0 = by * TY;
+    TileAt tile;
+    if (!tile_of_block<P>(geo, tile)) return;
+    const int z0 = tile.z0, z1 = tile.z1;
     const int t = threadIdx.x, tx = t % TX, ty = t / TX;
-    const bool active = (x0 + tx < geo.nx) && (y0 + ty < geo.ny);
-    // the lane just outside a ragged tile holds the periodic neighbour; those
-    // further out repeat it (nothing they compute is used)
-    const int x = x0 + tx < geo.nx ? x0 + tx : 0, y = y0 + ty < geo.ny ? y0 + ty : 0;
-
-    // this lane's ring site, if any: (rx, ry) in the tile's coordinates
+    const bool active = (tile.x0 + tx < geo.nx) && (tile.y0 + ty < geo.ny);
     int rx, ry;
-    if (t < 2 * TX) { rx = t % TX; ry = t < TX ? -1 : TY; }
-    else if (t < 2 * TX + 2 * TY) { rx = t < 2 * TX + TY ? -1 : TX; ry = (t - 2 * TX) % TY; }
-    else { rx = (t & 1) ? TX : -1; ry = (t & 2) ? TY : -1; }
-    const bool ring = t < NRING;
-    const int gx = x0 + rx, gy = y0 + ry;
-    const int xr = gx < 0 ? geo.nx - 1 : (gx < geo.nx ? gx : 0), yr = gy < 0 ? geo.ny - 1 : (gy < geo.ny ? gy : 0);
+    const bool ring = ring_site<P, true>(t, rx, ry);
+    const InPlane own = in_plane<S>(image_of(tile.x0 + tx, geo.nx), image_of(tile.y0 + ty, geo.ny), geo),
+                  around = in_plane<S>(image_of(tile.x0 + rx, geo.nx), image_of(tile.y0 + ry, geo.ny), geo);
+    auto pull = [&](int z, const InPlane& ip, S (&v)[Q]) { pull_plane<P, S, BLK, GATHER>(src, z, geo, ip, v); };
+    auto put = [&](S* to, int z, const S (&v)[Q]) {
+        const PlaneBase<S, BLK> pl(to, z, geo);
+        uint32_t off = own.at[4];
+        asm volatile("" : "+v"(off));
+        static_for<0, Q>([&](auto I) {
+            constexpr int i = decltype(I)::value;
+            put_at<P>(pl.template dir<i>(off), v[i]);
+        });
+    };
+    auto collide = [&](const T (&f)[Q], S (&o)[Q]) {
+        collide_single<COLL, S>(f, cp, [&](auto I, S v) { o[decltype(I)::value] = v; });
+    };
 
-    T f[Q];
-    load_site<P, GATHER, S, T, WIDE>(src, site_wrapped(x, y, wrap_plane(z0 - 1, geo.nz), geo), geo, f);
+    S next[Q];
+    pull(wrap_plane(z0 - 1, geo.nz), own, next);
     T level[9], rise1[5], rise2[5];      // kept: c_z = 0 and c_z > 0 of plane p - 1, c_z > 0 of plane p - 2
 #pragma unroll
     for (int k = 0; k < 9; ++k) level[k] = T(0);
@@ -664,31 +750,30 @@ __global__ __launch_bounds__(P::TPB, sizeof(S) == 8 ? 2 : 4) void k_single_pair(
     for (int p = z0 - 1; p <= z1; ++p) {
         S (*lds)[P::TPB] = moved[(p - z0) & 1];
         const int pw = wrap_plane(p, geo.nz);
-        auto send = [&](const T (&o)[Q], int ox, int oy) {
+        auto send = [&](const S (&o)[Q], int ox, int oy) {
             static_for<0, Q>([&](auto I) {
                 constexpr int i = decltype(I)::value;
                 if constexpr (cx(i) != 0 || cy(i) != 0) {
                     const int dx = ox + cx(i), dy = oy + cy(i);
-                    if (dx >= 0 && dx < TX && dy >= 0 && dy < TY) lds[planar_slot(i)][dy * TX + dx] = stored<S>(o[i]);
+                    if (dx >= 0 && dx < TX && dy >= 0 && dy < TY) lds[planar_slot(i)][dy * TX + dx] = o[i];
                 }
             });
         };
-        T o[Q];
-        collide_single<COLL, S>(f, o, cp);
+        T f[Q];
+        S o[Q];
+#pragma unroll
+        for (int i = 0; i < Q; ++i) f[i] = static_cast<T>(next[i]);
+        collide(f, o);
         send(o, tx, ty);
-        if constexpr (REC) {
-            if (active && p >= z0 && p < z1) {
-                const uint32_t off = offset_at<0, 0, 0>(site_wrapped(x, y, p, geo), geo);
-                static_for<0, Q>([&](auto I) {
-                    constexpr int i = decltype(I)::value;
-                    stg<P::nt_store, S, WIDE>(mid + i * geo.dstride, off, stored<S>(o[i]));
-                });
-            }
-        }
+        if constexpr (REC)
+            if (active && p >= z0 && p < z1) put(mid, p, o);
         if (ring) {
-            T r[Q], ro[Q];
-            load_site<P, GATHER, S, T, WIDE>(src, site_wrapped(xr, yr, pw, geo), geo, r);
-            collide_single<COLL, S>(r, ro, cp);
+            S r[Q], ro[Q];
+            T rf[Q];
+            pull(pw, around, r);
+#pragma unroll
+            for (int i = 0; i < Q; ++i) rf[i] = static_cast<T>(r[i]);
+            collide(rf, ro);
             send(ro, rx, ry);
         }
         __syncthreads();     // two buffers: plane p + 2 writes this one only after the next barrier
@@ -696,9 +781,9 @@ __global__ __launch_bounds__(P::TPB, sizeof(S) == 8 ? 2 : 4) void k_single_pair(
         static_for<0, Q>([&](auto I) {
             constexpr int i = decltype(I)::value;
             if constexpr (cx(i) != 0 || cy(i) != 0) g[i] = static_cast<T>(lds[planar_slot(i)][t]);
-            else g[i] = static_cast<T>(stored<S>(o[i]));
+            else g[i] = static_cast<T>(o[i]);
         });
-        if (p < z1) load_site<P, GATHER, S, T, WIDE>(src, site_wrapped(x, y, wrap_plane(p + 1, geo.nz), geo), geo, f);
+        if (p < z1) pull(wrap_plane(p + 1, geo.nz), own, next);
         T f2[Q];
         int ku = 0, kl = 0;
         static_for<0, Q>([&](auto I) {
@@ -708,12 +793,8 @@ __global__ __launch_bounds__(P::TPB, sizeof(S) == 8 ? 2 : 4) void k_single_pair(
             else f2[i] = g[i];
         });
         if (p > z0 && active) {
-            collide_single<COLL, S>(f2, o, cp);
-            const uint32_t off = offset_at<0, 0, 0>(site_wrapped(x, y, p - 1, geo), geo);
-            static_for<0, Q>([&](auto I) {
-                constexpr int i = decltype(I)::value;
-                stg<P::nt_store, S, WIDE>(dst + i * geo.dstride, off, stored<S>(o[i]));
-            });
+            collide(f2, o);
+            put(dst, p - 1, o);
         }
     }
 }
@@ -1652,7 +1733,7 @@ __global__ __launch_bounds__(P::TPB) void k_adjoint_binary_combine(const double*
 
 constexpr int CB = 256;
 
-__global__ __launch_bounds__(CB) void k_mask_count(const uint8_t* __restrict__ mask, uint32_t nsite,
+static __global__ __launch_bounds__(CB) void k_mask_count(const uint8_t* __restrict__ mask, uint32_t nsite,
                                                    int64_t* __restrict__ counts) {
     __shared__ int sh[CB];
     const uint32_t s = blockIdx.x * CB + threadIdx.x;
@@ -1666,7 +1747,7 @@ __global__ __launch_bounds__(CB) void k_mask_count(const uint8_t* __restrict__ m
 }
 
 // Exclusive scan of counts[0..nb) in place (one block); total -> *total.
-__global__ __launch_bounds__(CB) void k_scan_counts(int64_t* counts, int nb, int64_t* total) {
+static __global__ __launch_bounds__(CB) void k_scan_counts(int64_t* counts, int nb, int64_t* total) {
     __shared__ int64_t sh[CB];
     const int t = threadIdx.x;
     const int per = (nb + CB - 1) / CB;
@@ -1691,7 +1772,7 @@ __global__ __launch_bounds__(CB) void k_scan_counts(int64_t* counts, int nb, int
     if (t == CB - 1) *total = sh[CB - 1];
 }
 
-__global__ __launch_bounds__(CB) void k_mask_scatter(const uint8_t* __restrict__ mask, uint32_t nsite,
+static __global__ __launch_bounds__(CB) void k_mask_scatter(const uint8_t* __restrict__ mask, uint32_t nsite,
                                                      const int64_t* __restrict__ offsets,
                                                      int32_t* __restrict__ index) {
     __shared__ int sh[CB];
@@ -1760,7 +1841,7 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 constexpr int COPY_TPB = 256;
 constexpr int COPY_U = 4;
 
-__global__ __launch_bounds__(COPY_TPB) void k_stream_copy(const u32x4* __restrict__ src, u32x4* __restrict__ dst,
+static __global__ __launch_bounds__(COPY_TPB) void k_stream_copy(const u32x4* __restrict__ src, u32x4* __restrict__ dst,
                                                           uint64_t nwords) {
     const uint64_t base = (uint64_t)blockIdx.x * (COPY_TPB * COPY_U) + threadIdx.x;
     u32x4 v[COPY_U];

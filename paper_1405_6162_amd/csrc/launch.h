@@ -1,0 +1,805 @@
+// Host side of liblb.so below the C ABI: the context, its memory layout, the
+// launch policies and, per storage type, the launchers that queue kernels on
+// the context's stream.  The launchers are instantiated once per storage type
+// (launch_f64.hip, launch_f32.hip, launch_f16.hip), so the kernels of the
+// three compile side by side.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <cmath>
+#include <cstdint>
+#include <type_traits>
+#include <vector>
+
+#include "../../include/lb.h"
+#include "kernels.h"
+
+namespace lbl {
+
+using namespace lbk;
+
+// Launch policy of every kernel in the library but the single-pass binary
+// step (below): 64 x 4 sites per block, one site per lane, nontemporal
+// stores (the next step reads the values from HBM anyway), XCD-ordered
+// tiles.  Chosen by a sweep over tile shapes, sites per lane (1, 2, 4),
+// nontemporal loads/stores and direction padding on 128^3 and 256^3
+// lattices; the differences were within 5%.
+using Pol = Tiling<64, 4, 1, false, true, true>;
+// The same with ordinary stores: for states that stay in the 256 MB memory-side
+// cache (kCachedBytes, both copies of every distribution), from which the next
+// step then reads them.  us a step, ordinary / nontemporal stores: binary FP16
+// 96^3 34 / 47, 112^3 (213 MB) 44 / 65, FP32 48^3 11.3 / 14.8, FP64 64^3 31 / 35;
+// single fluid in pairs FP32 96^3 15.6 / 19.7, 112^3 22.9 / 30.0; beyond the
+// cache they lose: FP64 128^3 261 / 247, 256^3 1919 / 1819.
+template <class P> using Cached = Tiling<P::TX, P::TY, P::TZ, P::nt_load, false, P::xcd>;
+constexpr size_t kCachedBytes = 280000000;
+// Pol with 2 and 4 sites per lane along z (lb_params.vvl).
+using Pol2 = Tiling<64, 4, 2, false, true, true>;
+using Pol4 = Tiling<64, 4, 4, false, true, true>;
+constexpr int kCUs = 256;
+// Tiles of the single-pass binary step (k_binary_march).  A 64 x 8
+// tile has 144 halo sites per 512 against 136 per 256 for 64 x 4, so
+// the halo's phi gathers (mostly re-reads of neighbouring tiles' g) fall from
+// 53% to 28% of the sites gathered: measured A/B on one box, 64 x 8 is 6.5%
+// faster than 64 x 4 in FP64 at 256^3, 2% at 128^3, 3% in FP32 and 1% in FP16;
+// 64 x 16 and 32 x 16 were slower in every storage.  In FP32 and FP16 a
+// 128 x 4 tile, which has half the x-halo sites (whose gathers each hit
+// a cache line of their own, 2 or 4 bytes used), is used where its rows leave
+// no more lanes idle than 64-site rows (nx mod 128 is 0 or above 64): 200 x 204
+// x 100 289 against 297 us in FP32, 384^3 1817 against 1840 in FP16.
+// FP32 loads the ring's g early too with those tiles and, with 64 x 8 ones, from
+// kEarlyHaloSites up: 192^3 419 against 432 us, 320^3 1947 against 1996; 160^3
+// 261 against 250.
+using MarchTile = Tiling<64, 8, 1, false, true, true>;
+using MarchTileWide = Tiling<128, 4, 1, false, true, true>;
+// Blocks of the march the chip runs at once: one 512-lane block a CU where it
+// is compiled for two waves per SIMD (FP64, FP32), two for four (FP16).
+template <class S>
+constexpr int march_slots() { return kCUs * MarchHold<S, 64, false>::waves * 4 * 64 / MarchTile::TPB; }
+constexpr int64_t kEarlyHaloSites = 6000000;
+// Two single-fluid steps per launch (k_single_pair).  A CU holds one 512-lane
+// block in FP64 (128 KB of LDS, up to 256 VGPRs a lane), and 1024 lanes in
+// FP32 and FP16 (128 VGPRs): two blocks of 64 x 8 or, where 128-wide rows
+// leave no more lanes idle, one of 128 x 8 (256^3: 490 against 559 us a pair
+// in FP32, 355 against 384 in FP16).
+// From kPairMinSites up a pair beats two single steps, whose blocks each do
+// one plane where a pair's lead in and out over three; in FP16, whose pair is
+// bound by its arithmetic, only with no lanes idle besides.  us a step, in
+// pairs / single: FP64 48^3 8.8 / 8.6, 64^3 11.3 / 17.0, 256^3 478 / 896; FP32
+// 64^3 6.6 / 9.4, 256^3 250 / 453; FP16 112^3 24.5 / 24.4, 200 x 204 x 100 70.7 /
+// 67.3, 128^3 27.0 / 30.3, 256^3 177 / 225.
+template <class S>
+constexpr int64_t kPairMinSites = sizeof(S) == 8 ? 130000 : (sizeof(S) == 4 ? 200000 : 2000000);
+using PairTile = Tiling<64, 8, 1, false, true, true>;
+using PairTileWide = Tiling<128, 8, 1, false, true, true>;
+
+constexpr size_t kAlign = 4096;
+// Extra bytes between consecutive direction arrays, so the 19 (38) streams of
+// a power-of-two lattice do not start on the same HBM channel (measured:
+// 0 B padding is 5-10% slower than the best offsets; 9472 B = 37 x 256 B was
+// among the best on 128^3 and 256^3).
+constexpr size_t kDirPadBytes = 9472;
+
+inline size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
+
+inline size_t storage_size(int storage) { return storage == LB_F64 ? 8 : (storage == LB_F32 ? 4 : 2); }
+inline size_t compute_size(int storage) { return storage == LB_F64 ? 8 : 4; }
+
+struct Layout {
+    int64_t nsite;
+    int64_t dstride;        // elements between consecutive directions
+    bool blocked;           // 64-site blocks holding their 19 directions together
+    uint32_t zs, ys, xbs;   // site-offset strides (Geo)
+    size_t dist_bytes;      // one 19-direction buffer
+    size_t phi_bytes;
+    int nblocks;
+    size_t partial_bytes;
+    size_t off_f[2], off_g[2], off_phi, off_partial, total;
+};
+
+inline int check_params(const lb_params* p) {
+    if (!p) return LB_EINVAL;
+    if (p->nx < 1 || p->ny < 1 || p->nz < 1) return LB_EINVAL;
+    const int64_t n = (int64_t)p->nx * p->ny * p->nz;
+    // Kernels form byte offsets of FP64 arrays in 32 bits: N * 8 < 2^32.
+    if (n >= ((int64_t)1 << 29)) return LB_EINVAL;
+    if (p->model != LB_SINGLE && p->model != LB_BINARY) return LB_EINVAL;
+    if (p->storage != LB_F64 && p->storage != LB_F32 && p->storage != LB_F16) return LB_EINVAL;
+    if (p->vvl != 0 && p->vvl != 1 && p->vvl != 2 && p->vvl != 4) return LB_EINVAL;
+    if (p->binary_step < LB_STEP_AUTO || p->binary_step > LB_STEP_TWO_PASS) return LB_EINVAL;
+    if (p->collision != LB_BGK && p->collision != LB_TRT && p->collision != LB_MRT) return LB_EINVAL;
+    auto valid_tau = [](double t) { return std::isfinite(t) && t > 0.5; };
+    if (p->collision != LB_BGK && !valid_tau(p->tau_minus)) return LB_EINVAL;
+    if (p->collision == LB_MRT &&
+        (!valid_tau(p->tau_bulk) || !valid_tau(p->tau_ghost_even) || !valid_tau(p->tau_ghost_odd)))
+        return LB_EINVAL;
+    if (!std::isfinite(p->tau_f) || !(p->tau_f > 0.5)) return LB_EINVAL;
+    if (p->model == LB_BINARY) {
+        if (!std::isfinite(p->A) || !std::isfinite(p->B) || !std::isfinite(p->kappa)) return LB_EINVAL;
+        if (!(p->kappa >= 0.0)) return LB_EINVAL;
+        if (!std::isfinite(p->mobility) || !(p->mobility > 0.0)) return LB_EINVAL;
+        if (!std::isfinite(p->gamma) || !(p->gamma > 0.0)) return LB_EINVAL;
+    }
+    if (!std::isfinite(p->rho0) || !std::isfinite(p->phi0)) return LB_EINVAL;
+    return LB_OK;
+}
+
+inline Layout layout_of(const lb_params* p) {
+    Layout L{};
+    L.nsite = (int64_t)p->nx * p->ny * p->nz;
+    const size_t es = storage_size(p->storage);
+    // Blocked layout (see Geo) whenever a buffer's offsets fit in 32 bits
+    // (in bytes; for 4-byte elements, which are addressed by element, in
+    // elements);
+    // the last x block of a row is padded to 64 sites.  Measured A/B on one
+    // box against the structure-of-arrays layout: the single-fluid step
+    // +4.6% (FP64) and +5.6% (FP32) at 256^3, the binary march +4.3% (FP64,
+    // 256^3), +3.0% (FP64, 128^3), +3.6% (FP16, 384^3) and +2.5 to +5.6%
+    // (FP32, 128^3 to 256^3); padding between the buffers changed none of
+    // these.
+    const uint64_t xblocks = (uint64_t)tiles(p->nx, 64);
+    const uint64_t blocked_elems = (uint64_t)p->nz * (uint64_t)p->ny * xblocks * Q * 64;
+    L.blocked = (es == 4 ? blocked_elems : blocked_elems * es) < ((uint64_t)1 << 32);
+    if (L.blocked) {
+        L.dstride = 64;
+        L.xbs = Q * 64;
+        L.ys = (uint32_t)(xblocks * L.xbs);
+        L.zs = (uint32_t)((uint64_t)p->ny * L.ys);
+        L.dist_bytes = round_up((size_t)blocked_elems * es, kAlign);
+    } else {
+        const size_t stride_bytes = round_up((size_t)L.nsite * es, kAlign) + kDirPadBytes;
+        L.dstride = (int64_t)(stride_bytes / es);
+        L.xbs = 64;
+        L.ys = (uint32_t)p->nx;
+        L.zs = (uint32_t)p->nx * (uint32_t)p->ny;
+        L.dist_bytes = round_up(stride_bytes * Q, kAlign);
+    }
+    L.phi_bytes = round_up((size_t)L.nsite * compute_size(p->storage), kAlign);
+    L.nblocks = tiles(p->nx, Pol::TX) * tiles(p->ny, Pol::TY) * tiles(p->nz, Pol::TZ);
+    L.partial_bytes = round_up((size_t)L.nblocks * 16 * sizeof(double), kAlign);
+    size_t o = 0;
+    for (int b = 0; b < 2; ++b) { L.off_f[b] = o; o += L.dist_bytes; }
+    if (p->model == LB_BINARY) {
+        for (int b = 0; b < 2; ++b) { L.off_g[b] = o; o += L.dist_bytes; }
+        L.off_phi = o; o += L.phi_bytes;
+    } else {
+        L.off_g[0] = L.off_g[1] = L.off_phi = 0;
+    }
+    L.off_partial = o; o += L.partial_bytes;
+    L.total = o;
+    return L;
+}
+
+struct Rec { int kind; hipEvent_t start, stop; };
+
+}  // namespace lbl
+
+struct lb_ctx {
+    lb_params p;
+    lbl::Layout L;
+    hipStream_t stream;
+    char* ws;
+    int cur;          // buffer index holding the state
+    bool pending;     // true: the state is propagate(buffer[cur])
+    bool profiling;
+    unsigned profile_kinds;   // bit k: time launches of kernel class k
+    bool launched;    // any device work queued (lb_destroy waits for it)
+    std::vector<lbl::Rec> recs;
+    std::vector<hipEvent_t> pool;
+
+    lbk::Geo geo() const {
+        lbk::Geo g;
+        g.nx = p.nx; g.ny = p.ny; g.nz = p.nz;
+        g.plane = (uint32_t)p.nx * (uint32_t)p.ny;
+        g.nsite = (uint32_t)L.nsite;
+        g.dstride = L.dstride;
+        g.gx = lbk::tiles(p.nx, lbl::Pol::TX);
+        g.gy = lbk::tiles(p.ny, lbl::Pol::TY);
+        g.gz = lbk::tiles(p.nz, lbl::Pol::TZ);
+        g.nblocks = g.gx * g.gy * g.gz;
+        g.zs = L.zs; g.ys = L.ys; g.xbs = L.xbs;
+        return g;
+    }
+    // g with the layout of canonical caller arrays: direction stride N, x fastest
+    lbk::Geo canonical(lbk::Geo g) const {
+        g.dstride = L.nsite;
+        g.zs = g.plane; g.ys = (uint32_t)p.nx; g.xbs = 64;
+        return g;
+    }
+    lbk::Geo canonical_geo() const { return canonical(geo()); }
+    template <class P>
+    lbk::Geo geo_for() const {
+        lbk::Geo g = geo();
+        g.gz = lbk::tiles(p.nz, P::TZ);
+        g.nblocks = g.gx * g.gy * g.gz;
+        return g;
+    }
+    // Tiling of a marching kernel (k_binary_march, k_single_pair).  A chunk of
+    // d planes costs about d + 3 (its ends take two planes of phi, or of step
+    // one, more) and the chip runs `slots` blocks at a time: nz is cut, evenly,
+    // into the number of chunks (at most 128 planes each) that makes
+    // rounds x (d + 3) least.  Measured against fixed depths: pair, 256^3 FP64,
+    // 926 us with 2 chunks (one round), 1045 with 4; 128^3 128 with 8 (one
+    // round), 145 with 16.  March, FP64: 96^3 115 us with 10 chunks (240
+    // blocks), 148 with 6; 160^3 496 with 4 (one round), 520 with 8; 64^3 31
+    // with 32 chunks of 2 planes against 92 with 4 of 16 (the two-pass step: 40).
+    template <class TP>
+    lbk::Geo column_geo(int slots) const {
+        lbk::Geo g = geo();
+        g.gx = lbk::tiles(p.nx, TP::TX);
+        g.gy = lbk::tiles(p.ny, TP::TY);
+        const int64_t col = (int64_t)g.gx * g.gy;
+        int64_t best = INT64_MAX;
+        g.gz = 1;
+        for (int c = lbk::tiles(p.nz, 128); c <= p.nz; ++c) {
+            const int64_t cost = (col * c + slots - 1) / slots * (lbk::tiles(p.nz, c) + 3);
+            if (cost < best) { best = cost; g.gz = c; }
+        }
+        g.nblocks = g.gx * g.gy * g.gz;
+        return g;
+    }
+    // Whether the state stays in the memory-side cache (see Cached).
+    bool cached() const { return L.dist_bytes * (p.model == LB_BINARY ? 4 : 2) <= lbl::kCachedBytes; }
+    // Whether 128-wide tiles leave no more lanes of a row idle than 64-wide ones.
+    bool wide_rows() const { return lbk::tiles(p.nx, 128) * 2 == lbk::tiles(p.nx, 64); }
+    dim3 grid() const { return dim3(L.nblocks); }
+    static dim3 block() { return dim3(lbl::Pol::TPB); }
+    void* fbuf(int b) const { return ws + L.off_f[b]; }
+    void* gbuf(int b) const { return p.model == LB_BINARY ? ws + L.off_g[b] : nullptr; }
+    void* phi() const { return ws + L.off_phi; }
+    double* partial() const { return reinterpret_cast<double*>(ws + L.off_partial); }
+
+    // Timing-only events.  An ordinary event record ends with a system-scope
+    // fence (cache write-back and invalidation); between two dependent
+    // launches of the 128^3 binary step with profiling on, the rocprofv3
+    // kernel trace shows 11 us gaps with it and 8.5 us without.  Without it
+    // the profiled 64^3 adjoint rollout runs 12% faster and the 128^3 binary
+    // step 1%.  The events are only
+    // ever read by lb_kernel_times.
+    hipEvent_t take_event() {
+        if (!pool.empty()) { hipEvent_t e = pool.back(); pool.pop_back(); return e; }
+        hipEvent_t e = nullptr;
+        if (hipEventCreateWithFlags(&e, hipEventDisableSystemFence) != hipSuccess) return nullptr;
+        return e;
+    }
+    void release_records() {
+        for (auto& r : recs) { pool.push_back(r.start); pool.push_back(r.stop); }
+        recs.clear();
+    }
+};
+
+namespace lbl {
+
+// Brackets one launch with an event pair when profiling is on.
+struct Timed {
+    lb_ctx* c; int kind; hipEvent_t a = nullptr, b = nullptr;
+    Timed(lb_ctx* c_, int kind_) : c(c_), kind(kind_) {
+        if (c->profiling && ((c->profile_kinds >> kind) & 1u)) {
+            a = c->take_event(); b = c->take_event();
+            if (a && b) (void)hipEventRecord(a, c->stream);
+        }
+    }
+    ~Timed() {
+        if (a && b) {
+            (void)hipEventRecord(b, c->stream);
+            c->recs.push_back({kind, a, b});
+        } else {
+            if (a) c->pool.push_back(a);
+            if (b) c->pool.push_back(b);
+        }
+    }
+};
+
+inline int launch_status() { return hipGetLastError() == hipSuccess ? LB_OK : LB_EDEVICE; }
+
+
+
+template <class S>
+CollParams<typename Compute<S>::T> coll_params(const lb_ctx* c) {
+    using T = typename Compute<S>::T;
+    CollParams<T> cp;
+    cp.omega_f = (T)(1.0 / c->p.tau_f);
+    const double tau_g = c->p.model == LB_BINARY ? c->p.mobility / c->p.gamma + 0.5 : 1.0;
+    cp.omega_g = (T)(1.0 / tau_g);
+    cp.A = (T)c->p.A; cp.B = (T)c->p.B; cp.kappa = (T)c->p.kappa; cp.gamma = (T)c->p.gamma;
+    const bool dev = c->p.storage != LB_F64;
+    cp.rho0 = dev ? (T)c->p.rho0 : T(0);
+    cp.phi0 = dev ? (T)c->p.phi0 : T(0);
+    cp.omega_m = c->p.collision != LB_BGK ? (T)(1.0 / c->p.tau_minus) : cp.omega_f;
+    const bool mrt = c->p.collision == LB_MRT;
+    cp.omega_b = mrt ? (T)(1.0 / c->p.tau_bulk) : cp.omega_f;
+    cp.omega_ge = mrt ? (T)(1.0 / c->p.tau_ghost_even) : cp.omega_f;
+    cp.omega_go = mrt ? (T)(1.0 / c->p.tau_ghost_odd) : cp.omega_m;
+    return cp;
+}
+
+// ----- typed launchers ------------------------------------------------------
+
+// Calls fn with the launch policy of the context's sites per lane.
+template <class F>
+int by_vvl(const lb_ctx* c, F&& fn) {
+    switch (c->p.vvl) {
+        case 0: case 1: return c->cached() ? fn(Cached<Pol>{}) : fn(Pol{});
+        case 2: return fn(Pol2{});
+        case 4: return fn(Pol4{});
+    }
+    return LB_EINVAL;
+}
+
+template <class S>
+int run_phi(lb_ctx* c) {
+    using T = typename Compute<S>::T;
+    Timed t(c, LB_K_PHI);
+    const S* g = (const S*)c->gbuf(c->cur);
+    const T phi0 = coll_params<S>(c).phi0;
+    by_vvl(c, [&](auto pol) {
+        using P = decltype(pol);
+        const Geo geo = c->template geo_for<P>();
+        if (c->pending) k_phi<P, S, true><<<geo.nblocks, P::TPB, 0, c->stream>>>(g, (T*)c->phi(), geo, phi0);
+        else k_phi<P, S, false><<<geo.nblocks, P::TPB, 0, c->stream>>>(g, (T*)c->phi(), geo, phi0);
+        return 0;
+    });
+    return launch_status();
+}
+
+// Calls fn with the context's collision as an integral constant.
+template <class F>
+void by_collision(const lb_ctx* c, F&& fn) {
+    if (c->p.collision == LB_TRT) fn(std::integral_constant<int, COLL_TRT>{});
+    else if (c->p.collision == LB_MRT) fn(std::integral_constant<int, COLL_MRT>{});
+    else fn(std::integral_constant<int, COLL_BGK>{});
+}
+
+// One march from the pending state (fs, gs) to (fd, gd), all in the layout of
+// geo() or canonical; phi, if not NULL, receives the order parameter of the
+// state it collides.
+template <class S, bool BLK, bool PHI_OUT>
+int launch_march(lb_ctx* c, const S* fs, const S* gs, S* fd, S* gd, bool canonical, typename Compute<S>::T* phi) {
+    const auto cp = coll_params<S>(c);
+    auto with = [&](auto tiling, auto halo) {
+        using TP = decltype(tiling);
+        Geo g = c->template column_geo<TP>(march_slots<S>());
+        if (canonical) g = c->canonical(g);
+        Timed t(c, LB_K_COLLIDE);
+        by_collision(c, [&](auto coll) {
+            k_binary_march<TP, S, PHI_OUT, decltype(coll)::value, BLK, decltype(halo)::value>
+                <<<(unsigned)((g.nblocks + 7) / 8 * 8), TP::TPB, 0, c->stream>>>(fs, gs, fd, gd, g, cp, phi);
+        });
+    };
+    // records and structure-of-arrays states are far larger than the cache
+    auto launch = [&](auto tiling, auto halo) {
+        if constexpr (BLK && !PHI_OUT) {
+            if (c->cached()) { with(Cached<decltype(tiling)>{}, halo); return; }
+        }
+        with(tiling, halo);
+    };
+    constexpr std::integral_constant<bool, sizeof(S) == 4> fp32{};
+    if constexpr (sizeof(S) == 8) launch(MarchTile{}, std::false_type{});
+    else if (c->wide_rows()) launch(MarchTileWide{}, fp32);
+    else if (fp32 && c->L.nsite >= kEarlyHaloSites) launch(MarchTile{}, fp32);
+    else launch(MarchTile{}, std::false_type{});
+    return launch_status();
+}
+
+// Single-pass binary step from a pending buffer; on return the state is direct.
+template <class S>
+int run_binary_march(lb_ctx* c) {
+    const int src = c->cur, dst = 1 - c->cur;
+    const S* fs = (const S*)c->fbuf(src);
+    const S* gs = (const S*)c->gbuf(src);
+    S* fd = (S*)c->fbuf(dst);
+    S* gd = (S*)c->gbuf(dst);
+    const int rc = c->L.blocked ? launch_march<S, true, false>(c, fs, gs, fd, gd, false, nullptr)
+                                : launch_march<S, false, false>(c, fs, gs, fd, gd, false, nullptr);
+    if (rc) return rc;
+    c->cur = dst;
+    c->pending = false;
+    return LB_OK;
+}
+
+// Which binary step LB_STEP_AUTO takes.  One launch of the march beats the
+// two of the two-pass step (phi pass + fused collide, every site in parallel)
+// but on small FP64 lattices, whose few blocks each run a plane's gathers and
+// FP64 collision in sequence.  us a step, march / two-pass: FP64 48^3 24 / 22,
+// 64^3 34 / 39, 96^3 125 / 136; FP32 24^3 6.8 / 8.4, 48^3 14.9 / 14.6, 64^3 17 /
+// 22; FP16 24^3 7.3 / 8.4, 48^3 12.2 / 12.2, 96^3 47 / 54.
+// With more than one site per lane, which only the two-pass kernels have, from
+// the size up where one launch over whole tiles wins in any case.  The two
+// paths give the same bits.
+template <class S>
+bool march_pays(const lb_ctx* c) {
+    if (c->p.binary_step == LB_STEP_MARCH) return true;
+    if (c->p.binary_step == LB_STEP_TWO_PASS) return false;
+    if (c->p.vvl > 1) return c->L.nsite >= (int64_t)128 * 128 * 128;
+    return sizeof(S) != 8 || c->L.nsite >= 200000;
+}
+
+// One collision of the logical state; on return the state is direct.
+template <class S>
+int run_collide(lb_ctx* c) {
+    using T = typename Compute<S>::T;
+    const bool bin = c->p.model == LB_BINARY;
+    if (bin && c->pending && march_pays<S>(c)) return run_binary_march<S>(c);
+    if (bin) { int rc = run_phi<S>(c); if (rc) return rc; }
+    const auto cp = coll_params<S>(c);
+    const int src = c->cur, dst = c->pending ? 1 - c->cur : c->cur;
+    const S* fs = (const S*)c->fbuf(src); S* fd = (S*)c->fbuf(dst);
+    const S* gs = (const S*)c->gbuf(src); S* gd = (S*)c->gbuf(dst);
+    const T* phi = (const T*)c->phi();
+    {
+        Timed t(c, LB_K_COLLIDE);
+        by_vvl(c, [&](auto pol) {
+            using P = decltype(pol);
+            const Geo geo = c->template geo_for<P>();
+            const dim3 grid(geo.nblocks), block(P::TPB);
+            if (bin && c->p.collision == LB_TRT) {
+                if (c->pending) k_collide<P, MODEL_BINARY, S, true, COLL_TRT><<<grid, block, 0, c->stream>>>(fs, gs, fd, gd, phi, geo, cp);
+                else k_collide<P, MODEL_BINARY, S, false, COLL_TRT><<<grid, block, 0, c->stream>>>(fs, gs, fd, gd, phi, geo, cp);
+            } else if (bin && c->p.collision == LB_MRT) {
+                if (c->pending) k_collide<P, MODEL_BINARY, S, true, COLL_MRT><<<grid, block, 0, c->stream>>>(fs, gs, fd, gd, phi, geo, cp);
+                else k_collide<P, MODEL_BINARY, S, false, COLL_MRT><<<grid, block, 0, c->stream>>>(fs, gs, fd, gd, phi, geo, cp);
+            } else if (bin) {
+                if (c->pending) k_collide<P, MODEL_BINARY, S, true><<<grid, block, 0, c->stream>>>(fs, gs, fd, gd, phi, geo, cp);
+                else k_collide<P, MODEL_BINARY, S, false><<<grid, block, 0, c->stream>>>(fs, gs, fd, gd, phi, geo, cp);
+            } else if (c->p.collision == LB_TRT) {
+                if (c->pending) k_collide<P, MODEL_SINGLE, S, true, COLL_TRT><<<grid, block, 0, c->stream>>>(fs, gs, fd, gd, phi, geo, cp);
+                else k_collide<P, MODEL_SINGLE, S, false, COLL_TRT><<<grid, block, 0, c->stream>>>(fs, gs, fd, gd, phi, geo, cp);
+            } else if (c->p.collision == LB_MRT) {
+                if (c->pending) k_collide<P, MODEL_SINGLE, S, true, COLL_MRT><<<grid, block, 0, c->stream>>>(fs, gs, fd, gd, phi, geo, cp);
+                else k_collide<P, MODEL_SINGLE, S, false, COLL_MRT><<<grid, block, 0, c->stream>>>(fs, gs, fd, gd, phi, geo, cp);
+            } else {
+                if (c->pending) k_collide<P, MODEL_SINGLE, S, true><<<grid, block, 0, c->stream>>>(fs, gs, fd, gd, phi, geo, cp);
+                else k_collide<P, MODEL_SINGLE, S, false><<<grid, block, 0, c->stream>>>(fs, gs, fd, gd, phi, geo, cp);
+            }
+            return 0;
+        });
+    }
+    int rc = launch_status();
+    if (rc) return rc;
+    c->cur = dst;
+    c->pending = false;
+    return LB_OK;
+}
+
+// Copy a state (f, and g for the binary model) from layout sgeo to layout
+// dgeo, site by site (the context's layout <-> canonical caller memory), pulled
+// when GATHER.
+template <class S, bool GATHER>
+int run_copy(lb_ctx* c, const S* fs, const S* gs, S* fd, S* gd, const Geo& sgeo, const Geo& dgeo) {
+    auto with = [&](auto pol) {
+        using P = decltype(pol);
+        if (c->p.model == LB_BINARY)
+            k_stream2<P, S, GATHER><<<c->grid(), c->block(), 0, c->stream>>>(fs, gs, fd, gd, sgeo, dgeo);
+        else
+            k_stream<P, S, GATHER><<<c->grid(), c->block(), 0, c->stream>>>(fs, fd, sgeo, dgeo);
+        return launch_status();
+    };
+    return c->cached() ? with(Cached<Pol>{}) : with(Pol{});
+}
+
+// Materialise propagate(buffer[src]) into (f, g) of layout dgeo.
+template <class S>
+int run_stream_into(lb_ctx* c, int src, S* f, S* g, const Geo& dgeo) {
+    Timed t(c, LB_K_STREAM);
+    return run_copy<S, true>(c, (const S*)c->fbuf(src), (const S*)c->gbuf(src), f, g, c->geo(), dgeo);
+}
+
+template <class S>
+int run_convert(lb_ctx* c, const S* fs, const S* gs, S* fd, S* gd, const Geo& sgeo, const Geo& dgeo) {
+    return run_copy<S, false>(c, fs, gs, fd, gd, sgeo, dgeo);
+}
+
+template <class S>
+int run_propagate(lb_ctx* c) {
+    if (!c->pending) { c->pending = true; return LB_OK; }   // propagation of a direct buffer is deferred
+    const int dst = 1 - c->cur;
+    int rc = run_stream_into<S>(c, c->cur, (S*)c->fbuf(dst), (S*)c->gbuf(dst), c->geo());
+    if (rc) return rc;
+    c->cur = dst;
+    return LB_OK;
+}
+
+// Two collisions, with the propagation between them, of the state in `src`
+// (a pending one is pulled), into `dst`; REC: the first one's values into
+// `mid`.  All three in the layout of geo().
+template <class S, bool BLK, bool REC>
+int launch_single_pair(lb_ctx* c, bool pending, const S* src, S* mid, S* dst, bool canonical) {
+    const auto cp = coll_params<S>(c);
+    auto with = [&](auto tiling) {
+        using TP = decltype(tiling);
+        // FP64: one 512-lane block a CU; FP32, FP16: 1024 lanes
+        Geo g = c->template column_geo<TP>(kCUs * (sizeof(S) == 8 ? 1 : 1024 / TP::TPB));
+        if (canonical) g = c->canonical(g);
+        const dim3 grid((unsigned)((g.nblocks + 7) / 8 * 8)), block(TP::TPB);
+        Timed t(c, LB_K_COLLIDE);
+        by_collision(c, [&](auto coll) {
+            constexpr int COLL = decltype(coll)::value;
+            if (pending) k_single_pair<TP, S, true, COLL, BLK, REC><<<grid, block, 0, c->stream>>>(src, mid, dst, g, cp);
+            else k_single_pair<TP, S, false, COLL, BLK, REC><<<grid, block, 0, c->stream>>>(src, mid, dst, g, cp);
+        });
+    };
+    auto launch = [&](auto tiling) {
+        if constexpr (BLK && !REC) {
+            if (c->cached()) { with(Cached<decltype(tiling)>{}); return; }
+        }
+        with(tiling);
+    };
+    if constexpr (sizeof(S) < 8) {
+        if (c->wide_rows()) { launch(PairTileWide{}); return launch_status(); }
+    }
+    launch(PairTile{});
+    return launch_status();
+}
+
+// Whether two single-fluid steps run as one launch: not with more than one
+// site per lane (lb_params.vvl), nor on lattices too small or too large for
+// the blocked layout.
+template <class S>
+bool pair_pays(const lb_ctx* c) {
+    if (c->p.model != LB_SINGLE || c->p.vvl > 1 || !c->L.blocked || c->L.nsite < kPairMinSites<S>) return false;
+    return sizeof(S) > 2 || (c->p.nx % PairTile::TX == 0 && c->p.ny % PairTile::TY == 0);
+}
+
+template <class S>
+int run_step(lb_ctx* c, int32_t n) {
+    if (pair_pays<S>(c)) {
+        for (; n >= 2; n -= 2) {
+            const int rc = launch_single_pair<S, true, false>(c, c->pending, (const S*)c->fbuf(c->cur), nullptr,
+                                                              (S*)c->fbuf(1 - c->cur), false);
+            if (rc) return rc;
+            c->cur = 1 - c->cur;
+            c->pending = true;
+        }
+    }
+    for (int32_t k = 0; k < n; ++k) {
+        int rc = run_collide<S>(c);
+        if (rc) return rc;
+        c->pending = true;
+    }
+    return LB_OK;
+}
+
+template <class S>
+int run_init(lb_ctx* c, const double* rho, const double* u, const double* phi) {
+    Timed t(c, LB_K_OTHER);
+    CollParams<double> cp;
+    const auto ct = coll_params<S>(c);
+    cp.omega_f = ct.omega_f; cp.omega_g = ct.omega_g;
+    cp.A = c->p.A; cp.B = c->p.B; cp.kappa = c->p.kappa; cp.gamma = c->p.gamma;
+    cp.rho0 = c->p.storage == LB_F64 ? 0.0 : c->p.rho0;
+    cp.phi0 = c->p.storage == LB_F64 ? 0.0 : c->p.phi0;
+    S* f = (S*)c->fbuf(c->cur);
+    S* g = (S*)c->gbuf(c->cur);
+    if (c->p.model == LB_BINARY) k_init<Pol, MODEL_BINARY, S><<<c->grid(), c->block(), 0, c->stream>>>(rho, u, phi, f, g, c->geo(), cp);
+    else k_init<Pol, MODEL_SINGLE, S><<<c->grid(), c->block(), 0, c->stream>>>(rho, u, phi, f, g, c->geo(), cp);
+    int rc = launch_status();
+    if (rc == LB_OK) c->pending = false;
+    return rc;
+}
+
+template <class S>
+int run_moments(lb_ctx* c, double* rho, double* u, double* phi) {
+    Timed t(c, LB_K_OTHER);
+    const double r0 = c->p.storage == LB_F64 ? 0.0 : c->p.rho0;
+    const double p0 = c->p.storage == LB_F64 ? 0.0 : c->p.phi0;
+    const S* f = (const S*)c->fbuf(c->cur);
+    const S* g = (const S*)c->gbuf(c->cur);
+    const dim3 grid = c->grid(), block = c->block();
+    if (c->p.model == LB_BINARY) {
+        if (c->pending) k_moments<Pol, MODEL_BINARY, S, true><<<grid, block, 0, c->stream>>>(f, g, rho, u, phi, c->geo(), r0, p0);
+        else k_moments<Pol, MODEL_BINARY, S, false><<<grid, block, 0, c->stream>>>(f, g, rho, u, phi, c->geo(), r0, p0);
+    } else {
+        if (c->pending) k_moments<Pol, MODEL_SINGLE, S, true><<<grid, block, 0, c->stream>>>(f, g, rho, u, nullptr, c->geo(), r0, p0);
+        else k_moments<Pol, MODEL_SINGLE, S, false><<<grid, block, 0, c->stream>>>(f, g, rho, u, nullptr, c->geo(), r0, p0);
+    }
+    return launch_status();
+}
+
+// Sums of a state (f, g) in geo's layout into out, by way of `partial`; b0 and
+// b4 are added to sum rho and sum phi.
+template <class S>
+int sums_of(int model, const S* f, const S* g, const Geo& geo, double* partial, double b0, double b4, double* out,
+            hipStream_t s) {
+    if (model == LB_BINARY) k_sums_partial<Pol, MODEL_BINARY, S><<<geo.nblocks, Pol::TPB, 0, s>>>(f, g, geo, partial);
+    else k_sums_partial<Pol, MODEL_SINGLE, S><<<geo.nblocks, Pol::TPB, 0, s>>>(f, nullptr, geo, partial);
+    k_sums_final<Pol, 5><<<1, Pol::TPB, 0, s>>>(partial, geo.nblocks, out, b0, b4, 0);
+    return launch_status();
+}
+
+template <class S>
+int run_sums(lb_ctx* c, double* out) {
+    Timed t(c, LB_K_OTHER);
+    const bool dev = c->p.storage != LB_F64;
+    const double n = (double)c->L.nsite;
+    const double b0 = dev ? n * c->p.rho0 : 0.0;
+    const double b4 = (dev && c->p.model == LB_BINARY) ? n * c->p.phi0 : 0.0;
+    return sums_of<S>(c->p.model, (const S*)c->fbuf(c->cur), (const S*)c->gbuf(c->cur), c->geo(), c->partial(), b0,
+                      b4, out, c->stream);
+}
+
+template <class S>
+int run_stats(lb_ctx* c, double* out) {
+    Timed t(c, LB_K_OTHER);
+    const S* f = (const S*)c->fbuf(c->cur);
+    const S* g = (const S*)c->gbuf(c->cur);
+    const bool dev = c->p.storage != LB_F64;
+    const double r0 = dev ? c->p.rho0 : 0.0, p0 = dev ? c->p.phi0 : 0.0;
+    const Geo geo = c->geo();
+    const bool bin = c->p.model == LB_BINARY;
+    if (bin && c->pending)
+        k_stats_partial<Pol, MODEL_BINARY, S, true><<<c->grid(), c->block(), 0, c->stream>>>(f, g, geo, r0, p0, c->partial());
+    else if (bin)
+        k_stats_partial<Pol, MODEL_BINARY, S, false><<<c->grid(), c->block(), 0, c->stream>>>(f, g, geo, r0, p0, c->partial());
+    else if (c->pending)
+        k_stats_partial<Pol, MODEL_SINGLE, S, true><<<c->grid(), c->block(), 0, c->stream>>>(f, g, geo, r0, p0, c->partial());
+    else
+        k_stats_partial<Pol, MODEL_SINGLE, S, false><<<c->grid(), c->block(), 0, c->stream>>>(f, g, geo, r0, p0, c->partial());
+    k_stats_final<Pol><<<1, c->block(), 0, c->stream>>>(c->partial(), c->L.nblocks, out, bin ? 1 : 0);
+    return launch_status();
+}
+
+template <class S>
+int run_get_state(lb_ctx* c, S* f, S* g) {
+    if (c->pending) return run_stream_into<S>(c, c->cur, f, g, c->canonical_geo());
+    Timed t(c, LB_K_OTHER);
+    return run_convert<S>(c, (const S*)c->fbuf(c->cur), (const S*)c->gbuf(c->cur), f, g, c->geo(),
+                          c->canonical_geo());
+}
+
+template <class S>
+int run_set_state(lb_ctx* c, const S* f, const S* g) {
+    Timed t(c, LB_K_OTHER);
+    const int rc = run_convert<S>(c, f, g, (S*)c->fbuf(c->cur), (S*)c->gbuf(c->cur), c->canonical_geo(), c->geo());
+    if (rc) return rc;
+    c->pending = false;
+    return LB_OK;
+}
+
+// nsteps single-fluid steps whose post-collision fields go to post[k] (canonical
+// stride N); afterwards the state is pending on a copy of the last of them.
+// Binary: step k writes post-collision f then g at post + k*38*N.  Step 0
+// collides the context's state in its own buffers and copies the result out;
+// later steps march from post[k-1] to post[k] (both of direction stride N).
+template <class S>
+int run_step_record_binary(lb_ctx* c, int32_t n, S* post, typename Compute<S>::T* phi) {
+    using T = typename Compute<S>::T;
+    const int64_t N = c->L.nsite;
+    const auto cp = coll_params<S>(c);
+    if (phi) {                                        // phi of the state step 0 collides
+        Timed t(c, LB_K_PHI);
+        const S* g = (const S*)c->gbuf(c->cur);
+        if (c->pending) k_phi<Pol, S, true><<<c->grid(), c->block(), 0, c->stream>>>(g, phi, c->geo(), cp.phi0);
+        else k_phi<Pol, S, false><<<c->grid(), c->block(), 0, c->stream>>>(g, phi, c->geo(), cp.phi0);
+    }
+    int rc = run_collide<S>(c);                       // state now direct: the post-collision field
+    if (rc) return rc;
+    {
+        Timed t(c, LB_K_OTHER);
+        rc = run_convert<S>(c, (const S*)c->fbuf(c->cur), (const S*)c->gbuf(c->cur), post, post + Q * N, c->geo(),
+                            c->canonical_geo());
+        if (rc) return rc;
+    }
+    c->pending = true;
+    const bool march = march_pays<S>(c);
+    Geo cg = c->canonical_geo();
+    for (int32_t k = 1; k < n; ++k) {
+        const S* src = post + (size_t)(k - 1) * 2 * Q * N;
+        S* dst = post + (size_t)k * 2 * Q * N;
+        if (!march) {
+            // two-pass: phi of the recorded state, then the fused collide, both on stride N
+            T* ph = phi ? phi + (size_t)k * N : (T*)c->phi();
+            {
+                Timed t(c, LB_K_PHI);
+                k_phi<Pol, S, true><<<c->grid(), c->block(), 0, c->stream>>>(src + Q * N, ph, cg, cp.phi0);
+            }
+            {
+                Timed t(c, LB_K_COLLIDE);
+                if (c->p.collision == LB_TRT)
+                    k_collide<Pol, MODEL_BINARY, S, true, COLL_TRT><<<c->grid(), c->block(), 0, c->stream>>>(
+                        src, src + Q * N, dst, dst + Q * N, ph, cg, cp);
+                else if (c->p.collision == LB_MRT)
+                    k_collide<Pol, MODEL_BINARY, S, true, COLL_MRT><<<c->grid(), c->block(), 0, c->stream>>>(
+                        src, src + Q * N, dst, dst + Q * N, ph, cg, cp);
+                else
+                    k_collide<Pol, MODEL_BINARY, S, true><<<c->grid(), c->block(), 0, c->stream>>>(
+                        src, src + Q * N, dst, dst + Q * N, ph, cg, cp);
+            }
+            rc = launch_status();
+            if (rc) return rc;
+            continue;
+        }
+        if (phi)
+            rc = launch_march<S, false, true>(c, src, src + Q * N, dst, dst + Q * N, true, phi + (size_t)k * N);
+        else
+            rc = launch_march<S, false, false>(c, src, src + Q * N, dst, dst + Q * N, true, nullptr);
+        if (rc) return rc;
+    }
+    if (n > 1) {
+        Timed t(c, LB_K_OTHER);
+        const S* last = post + (size_t)(n - 1) * 2 * Q * N;
+        rc = run_convert<S>(c, last, last + Q * N, (S*)c->fbuf(c->cur), (S*)c->gbuf(c->cur), c->canonical_geo(),
+                            c->geo());
+        if (rc) return rc;
+    }
+    return LB_OK;
+}
+
+template <class S>
+int run_step_record(lb_ctx* c, int32_t n, S* post, typename Compute<S>::T* phi) {
+    if (c->p.model == LB_BINARY) return run_step_record_binary<S>(c, n, post, phi);
+    const int64_t N = c->L.nsite;
+    const auto cp = coll_params<S>(c);
+    const dim3 grid = c->grid(), block = c->block();
+    // one collision from src (layout sg; pull from a pending src when GATHER)
+    // into canonical dst, for the context's collision
+    const Geo cg = c->canonical_geo();
+    auto collide = [&](auto gather, const S* src, const Geo& sg, S* dst) {
+        constexpr bool G = decltype(gather)::value;
+        if (c->p.collision == LB_TRT)
+            k_collide_single_strided<Pol, S, G, COLL_TRT><<<grid, block, 0, c->stream>>>(src, dst, sg, cg, cp);
+        else if (c->p.collision == LB_MRT)
+            k_collide_single_strided<Pol, S, G, COLL_MRT><<<grid, block, 0, c->stream>>>(src, dst, sg, cg, cp);
+        else
+            k_collide_single_strided<Pol, S, G><<<grid, block, 0, c->stream>>>(src, dst, sg, cg, cp);
+    };
+    for (int32_t k = 0; k < n; ++k) {
+        S* dst = post + (size_t)k * Q * N;
+        {
+            Timed t(c, LB_K_COLLIDE);
+            if (k == 0) {
+                const S* src = (const S*)c->fbuf(c->cur);
+                if (c->pending) collide(std::true_type{}, src, c->geo(), dst);
+                else collide(std::false_type{}, src, c->geo(), dst);
+            } else {
+                collide(std::true_type{}, post + (size_t)(k - 1) * Q * N, cg, dst);
+            }
+        }
+        int rc = launch_status();
+        if (rc) return rc;
+    }
+    Timed t(c, LB_K_OTHER);
+    const int rc = run_convert<S>(c, post + (size_t)(n - 1) * Q * N, nullptr, (S*)c->fbuf(c->cur), nullptr, cg,
+                                  c->geo());
+    if (rc) return rc;
+    c->pending = true;
+    return LB_OK;
+}
+
+template <class S>
+int run_sites(lb_ctx* c, const int32_t* index, int64_t m, S* f, S* g, bool set) {
+    Timed t(c, LB_K_OTHER);
+    const int nb = (int)((m + CB - 1) / CB);
+    const Geo geo = c->geo();
+    S* bufs[2] = {(S*)c->fbuf(c->cur), (S*)c->gbuf(c->cur)};
+    S* packs[2] = {f, g};
+    for (int d = 0; d < (c->p.model == LB_BINARY ? 2 : 1); ++d) {
+        if (set) {
+            if (c->pending) k_set_sites<S, true><<<nb, CB, 0, c->stream>>>(bufs[d], index, m, packs[d], geo);
+            else k_set_sites<S, false><<<nb, CB, 0, c->stream>>>(bufs[d], index, m, packs[d], geo);
+        } else {
+            if (c->pending) k_get_sites<S, true><<<nb, CB, 0, c->stream>>>(bufs[d], index, m, packs[d], geo);
+            else k_get_sites<S, false><<<nb, CB, 0, c->stream>>>(bufs[d], index, m, packs[d], geo);
+        }
+    }
+    return launch_status();
+}
+
+// The launchers of one storage type: LB_LAUNCHERS(template, S) instantiates
+// them, LB_LAUNCHERS(extern template, S) refers to another file's.
+#define LB_LAUNCHERS(what, S)                                                                                     \
+    what int run_collide<S>(lb_ctx*);                                                                             \
+    what int run_propagate<S>(lb_ctx*);                                                                           \
+    what int run_step<S>(lb_ctx*, int32_t);                                                                       \
+    what int run_init<S>(lb_ctx*, const double*, const double*, const double*);                                   \
+    what int run_moments<S>(lb_ctx*, double*, double*, double*);                                                  \
+    what int sums_of<S>(int, const S*, const S*, const Geo&, double*, double, double, double*, hipStream_t);      \
+    what int run_sums<S>(lb_ctx*, double*);                                                                       \
+    what int run_stats<S>(lb_ctx*, double*);                                                                      \
+    what int run_get_state<S>(lb_ctx*, S*, S*);                                                                   \
+    what int run_set_state<S>(lb_ctx*, const S*, const S*);                                                       \
+    what int run_step_record<S>(lb_ctx*, int32_t, S*, typename Compute<S>::T*);                                   \
+    what int run_sites<S>(lb_ctx*, const int32_t*, int64_t, S*, S*, bool);
+
+}  // namespace lbl

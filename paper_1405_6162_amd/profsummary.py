@@ -54,7 +54,7 @@ def kernel_source_digest():
     """sha256 of the kernel sources' code (comments and whitespace removed);
     a counter summary is stale once it changes."""
     h = hashlib.sha256()
-    for name in ("d3q19.h", "kernels.h", "lb_api.hip"):
+    for name in ("d3q19.h", "kernels.h", "launch.h", "lb_api.hip"):
         with open(os.path.join(PKG, "csrc", name), encoding="utf-8") as fh:
             h.update(_code_only(fh.read()).encode())
     return h.hexdigest()[:16]

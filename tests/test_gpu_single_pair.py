@@ -5,7 +5,8 @@ time it never does, so n single-step calls are the reference: the collision
 is written with explicit roundings, and the same bits are expected.  The
 shapes sit at the edges of the kernel's tiles (64 x 8 columns; 128 x 8 in
 FP32 and FP16 where nx mod 128 is 0 or above 64) and chunks: one site over,
-one short, exact, an extent of one and of two, several rounds of chunks.
+one short, exact, an extent of one and of two, several rounds of chunks, and
+on either side of the state size up to which the stores are ordinary ones.
 Odd step counts end with a single step; a count of 2 from a fresh state
 starts from a direct (unpropagated) one, 3 + 4 from a pending one.  One case
 is held to the C oracle as well (FP64, 1e-12 relative to the largest value,
@@ -22,10 +23,10 @@ from paper_1405_6162_amd import inputs
 pytestmark = pytest.mark.gpu
 
 SHAPES = {
-    "f64": [(67, 9, 80), (64, 8, 96), (129, 25, 17), (1, 223, 217), (2, 160, 155), (63, 7, 111), (256, 200, 1),
-            (128, 250, 2)],
-    "f32": [(67, 45, 67), (128, 40, 40), (127, 33, 49), (193, 41, 26), (320, 320, 2)],
-    "f16": [(150, 70, 90), (128, 83, 81), (129, 65, 103)],
+    "f64": [(67, 9, 216), (64, 8, 255), (129, 25, 41), (1, 367, 357), (2, 260, 255), (63, 7, 297), (256, 512, 1),
+            (256, 256, 2), (130, 91, 89)],
+    "f32": [(67, 45, 67), (128, 40, 40), (127, 33, 49), (193, 41, 26), (320, 320, 2), (200, 97, 101)],
+    "f16": [(128, 128, 123), (64, 256, 123), (192, 104, 101)],
 }
 COLL = {"bgk": {}, "trt": dict(collision=1, tau_minus=1.25),
         "mrt": dict(collision=2, tau_minus=1.25, tau_bulk=1.4, tau_ghost_even=0.9, tau_ghost_odd=1.2)}
@@ -61,7 +62,7 @@ def test_pairs_equal_single_steps(lbgpu, storage, nx, ny, nz, coll):
 
 
 def test_pairs_against_oracle(lbgpu):
-    nx, ny, nz = 67, 9, 80
+    nx, ny, nz = 67, 9, 216
     print("case single %dx%dx%d FP64 x5, pairs vs C oracle" % (nx, ny, nz), flush=True)
     rho, u = _fields(nx, ny, nz)
     C.set_threads(0)
