@@ -204,8 +204,7 @@ __device__ __forceinline__ bool ring_site(int k, int& rx, int& ry) {
 __device__ __forceinline__ int image_of(int x, int n) { return x < 0 ? n - 1 : (x < n ? x : 0); }
 
 template <class P>
-__device__ __forceinline__ Column column_of_thread(const Geo& g) {
-    const int b = tile_index<P>(g);
+__device__ __forceinline__ Column column_of_tile(const Geo& g, int b) {
     const int bx = b % g.gx;
     const int t = b / g.gx;
     const int by = t % g.gy;
@@ -221,6 +220,11 @@ __device__ __forceinline__ Column column_of_thread(const Geo& g) {
     c.ym = c.y == 0 ? g.ny - 1 : c.y - 1;
     c.yp = c.y + 1 >= g.ny ? 0 : c.y + 1;
     return c;
+}
+
+template <class P>
+__device__ __forceinline__ Column column_of_thread(const Geo& g) {
+    return column_of_tile<P>(g, tile_index<P>(g));
 }
 
 __device__ __forceinline__ Site site_at(const Column& c, int v, const Geo& g) {

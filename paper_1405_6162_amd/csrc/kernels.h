@@ -957,32 +957,75 @@ __device__ __forceinline__ void block_tree_sum(const double (&v)[K], double (*sh
     }
 }
 
+// Sum (or minimum, maximum: `op`) over the block of K values per thread, in a
+// fixed order; thread 64 w of wavefront w hands total k of those with
+// k mod (TPB / 64) == w to put(k, total).  The wavefronts share the values out,
+// so each only shuffles K / 4 of them.
+template <int TPB, int K, class OP, class F>
+__device__ __forceinline__ void block_reduce(const double (&v)[K], OP&& op, F&& put) {
+    constexpr int W = TPB / 64;
+    __shared__ double sh[K][TPB];
+    const int t = threadIdx.x, lane = t & 63;
+#pragma unroll
+    for (int k = 0; k < K; ++k) sh[k][t] = v[k];
+    __syncthreads();
+    for (int k = t >> 6; k < K; k += W) {
+        double r = sh[k][lane];
+#pragma unroll
+        for (int w = 1; w < W; ++w) r = op(k, r, sh[k][lane + 64 * w]);
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1) r = op(k, r, __shfl_down(r, d, 64));
+        if (lane == 0) put(k, r);
+    }
+}
+
+// Calls fn(site) for the sites of this block's share of the lattice's tiles:
+// `gridDim.x` blocks take contiguous runs of tiles, in XCD order, so a block
+// sums many tiles in registers and is reduced once.  (One reduction per tile
+// left 65536 partial sums at 256^3, and the single block that added them took
+// 0.2-0.3 ms beside the 0.9 ms of reading the state.)
+template <class P, class F>
+__device__ __forceinline__ void for_sites(const Geo& geo, F&& fn) {
+    int b = blockIdx.x;
+    const int n = gridDim.x;
+    if (P::xcd && (n & 7) == 0) b = (b & 7) * (n >> 3) + (b >> 3);
+    const int t0 = (int)((int64_t)b * geo.nblocks / n), t1 = (int)((int64_t)(b + 1) * geo.nblocks / n);
+    for (int t = t0; t < t1; ++t) {
+        const Column col = column_of_tile<P>(geo, t);
+        for (int v = 0; v < P::TZ; ++v) {
+            const Site st = site_at(col, v, geo);
+            if (st.active) fn(st);
+        }
+    }
+}
+
 // Local sums of the stored values (streaming permutes values, so the sums of
 // a pending buffer equal those of the state it stands for, up to the order
 // of the additions).
 template <class P, int MODEL, class S>
 __global__ __launch_bounds__(P::TPB) void k_sums_partial(const S* __restrict__ f, const S* __restrict__ g, Geo geo,
                                                          double* __restrict__ partial) {
-    __shared__ double sh[5][P::TPB];
-    const Column col = column_of_thread<P>(geo);
     double v5[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    for (int v = 0; v < P::TZ; ++v) {
-        const Site st = site_at(col, v, geo);
-        if (!st.active) continue;
+    for_sites<P>(geo, [&](const Site& st) {
         const uint32_t off = offset_at<0, 0, 0>(st, geo);
+        S fv[Q], gv[MODEL == MODEL_BINARY ? Q : 1];      // all loads of a site go out as one batch
         static_for<0, Q>([&](auto I) {
             constexpr int i = decltype(I)::value;
-            const double a = static_cast<double>(*at(f + i * geo.dstride, off));
+            fv[i] = *at(f + i * geo.dstride, off);
+            if constexpr (MODEL == MODEL_BINARY) gv[i] = *at(g + i * geo.dstride, off);
+        });
+        static_for<0, Q>([&](auto I) {
+            constexpr int i = decltype(I)::value;
+            const double a = static_cast<double>(fv[i]);
             v5[0] = v5[0] + a;
             if constexpr (cx(i) != 0) v5[1] = v5[1] + cx(i) * a;
             if constexpr (cy(i) != 0) v5[2] = v5[2] + cy(i) * a;
             if constexpr (cz(i) != 0) v5[3] = v5[3] + cz(i) * a;
-            if constexpr (MODEL == MODEL_BINARY) v5[4] = v5[4] + static_cast<double>(*at(g + i * geo.dstride, off));
+            if constexpr (MODEL == MODEL_BINARY) v5[4] = v5[4] + static_cast<double>(gv[i]);
         });
-    }
-    block_tree_sum<P::TPB, 5>(v5, sh);
-    const int t = threadIdx.x;
-    if (t < 5) partial[8 * (size_t)blockIdx.x + t] = sh[t][0];
+    });
+    block_reduce<P::TPB>(v5, [](int, double a, double b) { return a + b; },
+                         [&](int k, double r) { partial[8 * (size_t)blockIdx.x + k] = r; });
 }
 
 // out[k] = base[k] + sum_b partial[8 b + k], k < K; one block of P::TPB threads.
@@ -1024,38 +1067,27 @@ __global__ __launch_bounds__(P::TPB) void k_sums_final(const double* __restrict_
 
 constexpr int NSTAT = 10;
 
-template <int TPB>
-__device__ __forceinline__ void block_tree_stats(double (&v)[NSTAT], double (*sh)[TPB]) {
-    const int t = threadIdx.x;
-#pragma unroll
-    for (int k = 0; k < NSTAT; ++k) sh[k][t] = v[k];
-    __syncthreads();
-    for (int half = TPB / 2; half > 0; half >>= 1) {
-        if (t < half) {
-#pragma unroll
-            for (int k = 0; k < NSTAT; ++k) {
-                const double a = sh[k][t], b = sh[k][t + half];
-                sh[k][t] = k == 6 ? fmin(a, b) : (k == 7 || k == 9 ? fmax(a, b) : a + b);
-            }
-        }
-        __syncthreads();
-    }
+__device__ __forceinline__ double combine_stat(int k, double a, double b) {
+    return k == 6 ? fmin(a, b) : (k == 7 || k == 9 ? fmax(a, b) : a + b);
 }
 
 template <class P, int MODEL, class S, bool GATHER>
 __global__ __launch_bounds__(P::TPB) void k_stats_partial(const S* __restrict__ f, const S* __restrict__ g, Geo geo,
                                                           double rho0, double phi0, double* __restrict__ partial) {
-    __shared__ double sh[NSTAT][P::TPB];
-    const Column col = column_of_thread<P>(geo);
     double v[NSTAT] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, INFINITY, -INFINITY, 0.0, 0.0};
-    for (int z = 0; z < P::TZ; ++z) {
-        const Site st = site_at(col, z, geo);
-        if (!st.active) continue;
+    for_sites<P>(geo, [&](const Site& st) {
         double fv[Q];
         static_for<0, Q>([&](auto I) {
             constexpr int i = decltype(I)::value;
             fv[i] = static_cast<double>(*at(f + i * geo.dstride, src_offset<i, GATHER>(st, geo)));
         });
+        double gv[MODEL == MODEL_BINARY ? Q : 1];
+        if constexpr (MODEL == MODEL_BINARY) {
+            static_for<0, Q>([&](auto I) {
+                constexpr int i = decltype(I)::value;
+                gv[i] = static_cast<double>(*at(g + i * geo.dstride, src_offset<i, GATHER>(st, geo)));
+            });
+        }
         double drho, jx, jy, jz;
         moments_of(fv, drho, jx, jy, jz);
         const double rho = rho0 + drho;
@@ -1065,38 +1097,31 @@ __global__ __launch_bounds__(P::TPB) void k_stats_partial(const S* __restrict__ 
         v[9] = fmax(v[9], uu);
         if constexpr (MODEL == MODEL_BINARY) {
             double acc = 0.0;
-            static_for<0, Q>([&](auto I) {
-                constexpr int i = decltype(I)::value;
-                acc = acc + static_cast<double>(*at(g + i * geo.dstride, src_offset<i, GATHER>(st, geo)));
-            });
+            for (int i = 0; i < Q; ++i) acc = acc + gv[i];
             const double phi = phi0 + acc;
             v[4] += phi;
             v[6] = fmin(v[6], phi);
             v[7] = fmax(v[7], phi);
             v[8] += phi * phi;
         }
-    }
-    block_tree_stats<P::TPB>(v, sh);
-    if ((int)threadIdx.x < NSTAT) partial[16 * (size_t)blockIdx.x + threadIdx.x] = sh[threadIdx.x][0];
+    });
+    block_reduce<P::TPB>(v, combine_stat, [&](int k, double r) { partial[16 * (size_t)blockIdx.x + k] = r; });
 }
 
 template <class P>
 __global__ __launch_bounds__(P::TPB) void k_stats_final(const double* __restrict__ partial, int nblocks,
                                                         double* __restrict__ out, int binary) {
-    __shared__ double sh[NSTAT][P::TPB];
     const int t = threadIdx.x;
     double v[NSTAT] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, INFINITY, -INFINITY, 0.0, 0.0};
     for (int b = t; b < nblocks; b += P::TPB) {
         const double* q = partial + 16 * (size_t)b;
 #pragma unroll
-        for (int k = 0; k < NSTAT; ++k)
-            v[k] = k == 6 ? fmin(v[k], q[k]) : (k == 7 || k == 9 ? fmax(v[k], q[k]) : v[k] + q[k]);
+        for (int k = 0; k < NSTAT; ++k) v[k] = combine_stat(k, v[k], q[k]);
     }
-    block_tree_stats<P::TPB>(v, sh);
-    if (t == 0) {
-        for (int k = 0; k < NSTAT; ++k) out[k] = sh[k][0];
-        if (!binary) { out[4] = 0.0; out[6] = 0.0; out[7] = 0.0; out[8] = 0.0; }
-    }
+    block_reduce<P::TPB>(v, combine_stat, [&](int k, double r) {
+        const bool of_phi = k == 4 || (k >= 6 && k <= 8);
+        out[k] = of_phi && !binary ? 0.0 : r;
+    });
 }
 
 // ---------------------------------------------------------------------------
@@ -1727,23 +1752,49 @@ __global__ __launch_bounds__(P::TPB) void k_adjoint_binary_combine(const double*
 // is compacted, in increasing site order, into a list of site indices; the
 // state at the listed sites is then gathered into or scattered from a packed
 // direction-major array [19][m].  Compaction is three deterministic passes
-// over blocks of CB consecutive sites: count, scan of the block counts, and
-// a scatter that scans each block's flags in LDS.
+// over blocks of CB * CM consecutive sites, CM to a lane: count, scan of the
+// block counts, and a scatter that scans the lanes' counts.  (With one site a
+// lane the scan, one block adding 65536 counts at 256^3, took most of it.)
 // ---------------------------------------------------------------------------
 
 constexpr int CB = 256;
+constexpr int CM = 16;
 
-static __global__ __launch_bounds__(CB) void k_mask_count(const uint8_t* __restrict__ mask, uint32_t nsite,
-                                                   int64_t* __restrict__ counts) {
+// Bit k: mask[s0 + k] is set, for the lane's CM sites from s0 on.
+static __device__ __forceinline__ uint32_t mask_bits(const uint8_t* __restrict__ mask, uint32_t s0, uint32_t nsite) {
+    uint32_t bits = 0;
+    if (s0 + CM <= nsite && (reinterpret_cast<uintptr_t>(mask) & 15) == 0) {       // s0 is a multiple of CM
+        const uint4 w = *reinterpret_cast<const uint4*>(mask + s0);
+        const uint32_t q[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+        for (int k = 0; k < CM; ++k) bits |= ((q[k >> 2] >> (8 * (k & 3)) & 0xffu) != 0 ? 1u : 0u) << k;
+    } else {
+        for (int k = 0; k < CM; ++k)
+            if (s0 + k < nsite && mask[s0 + k] != 0) bits |= 1u << k;
+    }
+    return bits;
+}
+
+// Inclusive sum of one integer per lane over the block.
+static __device__ __forceinline__ int block_scan(int v) {
     __shared__ int sh[CB];
-    const uint32_t s = blockIdx.x * CB + threadIdx.x;
-    sh[threadIdx.x] = (s < nsite && mask[s] != 0) ? 1 : 0;
+    const int t = threadIdx.x;
+    sh[t] = v;
     __syncthreads();
-    for (int half = CB / 2; half > 0; half >>= 1) {
-        if ((int)threadIdx.x < half) sh[threadIdx.x] += sh[threadIdx.x + half];
+    for (int d = 1; d < CB; d <<= 1) {
+        const int w = t >= d ? sh[t - d] : 0;
+        __syncthreads();
+        sh[t] += w;
         __syncthreads();
     }
-    if (threadIdx.x == 0) counts[blockIdx.x] = sh[0];
+    return sh[t];
+}
+
+static __global__ __launch_bounds__(CB) void k_mask_count(const uint8_t* __restrict__ mask, uint32_t nsite,
+                                                          int64_t* __restrict__ counts) {
+    const uint32_t s0 = (blockIdx.x * CB + threadIdx.x) * CM;
+    const int total = block_scan(__popc(mask_bits(mask, s0, nsite)));
+    if (threadIdx.x == CB - 1) counts[blockIdx.x] = total;
 }
 
 // Exclusive scan of counts[0..nb) in place (one block); total -> *total.
@@ -1773,20 +1824,13 @@ static __global__ __launch_bounds__(CB) void k_scan_counts(int64_t* counts, int 
 }
 
 static __global__ __launch_bounds__(CB) void k_mask_scatter(const uint8_t* __restrict__ mask, uint32_t nsite,
-                                                     const int64_t* __restrict__ offsets,
-                                                     int32_t* __restrict__ index) {
-    __shared__ int sh[CB];
-    const uint32_t s = blockIdx.x * CB + threadIdx.x;
-    const int flag = (s < nsite && mask[s] != 0) ? 1 : 0;
-    sh[threadIdx.x] = flag;
-    __syncthreads();
-    for (int d = 1; d < CB; d <<= 1) {
-        const int v = (int)threadIdx.x >= d ? sh[threadIdx.x - d] : 0;
-        __syncthreads();
-        sh[threadIdx.x] += v;
-        __syncthreads();
-    }
-    if (flag) index[offsets[blockIdx.x] + sh[threadIdx.x] - 1] = (int32_t)s;
+                                                            const int64_t* __restrict__ offsets,
+                                                            int32_t* __restrict__ index) {
+    const uint32_t s0 = (blockIdx.x * CB + threadIdx.x) * CM;
+    uint32_t bits = mask_bits(mask, s0, nsite);
+    const int own = __popc(bits);
+    int64_t to = offsets[blockIdx.x] + block_scan(own) - own;
+    for (; bits != 0; bits &= bits - 1) index[to++] = (int32_t)(s0 + __ffs(bits) - 1);
 }
 
 // Site s as coordinates with periodic neighbours.

@@ -597,14 +597,18 @@ int run_moments(lb_ctx* c, double* rho, double* u, double* phi) {
     return launch_status();
 }
 
+// Blocks of a reduction over the lattice: eight 256-lane ones a CU.
+constexpr int kReduceBlocks = 8 * kCUs;
+
 // Sums of a state (f, g) in geo's layout into out, by way of `partial`; b0 and
 // b4 are added to sum rho and sum phi.
 template <class S>
 int sums_of(int model, const S* f, const S* g, const Geo& geo, double* partial, double b0, double b4, double* out,
             hipStream_t s) {
-    if (model == LB_BINARY) k_sums_partial<Pol, MODEL_BINARY, S><<<geo.nblocks, Pol::TPB, 0, s>>>(f, g, geo, partial);
-    else k_sums_partial<Pol, MODEL_SINGLE, S><<<geo.nblocks, Pol::TPB, 0, s>>>(f, nullptr, geo, partial);
-    k_sums_final<Pol, 5><<<1, Pol::TPB, 0, s>>>(partial, geo.nblocks, out, b0, b4, 0);
+    const int nb = std::min(geo.nblocks, kReduceBlocks);
+    if (model == LB_BINARY) k_sums_partial<Pol, MODEL_BINARY, S><<<nb, Pol::TPB, 0, s>>>(f, g, geo, partial);
+    else k_sums_partial<Pol, MODEL_SINGLE, S><<<nb, Pol::TPB, 0, s>>>(f, nullptr, geo, partial);
+    k_sums_final<Pol, 5><<<1, Pol::TPB, 0, s>>>(partial, nb, out, b0, b4, 0);
     return launch_status();
 }
 
@@ -628,15 +632,16 @@ int run_stats(lb_ctx* c, double* out) {
     const double r0 = dev ? c->p.rho0 : 0.0, p0 = dev ? c->p.phi0 : 0.0;
     const Geo geo = c->geo();
     const bool bin = c->p.model == LB_BINARY;
+    const int nb = std::min(c->L.nblocks, kReduceBlocks);
     if (bin && c->pending)
-        k_stats_partial<Pol, MODEL_BINARY, S, true><<<c->grid(), c->block(), 0, c->stream>>>(f, g, geo, r0, p0, c->partial());
+        k_stats_partial<Pol, MODEL_BINARY, S, true><<<nb, c->block(), 0, c->stream>>>(f, g, geo, r0, p0, c->partial());
     else if (bin)
-        k_stats_partial<Pol, MODEL_BINARY, S, false><<<c->grid(), c->block(), 0, c->stream>>>(f, g, geo, r0, p0, c->partial());
+        k_stats_partial<Pol, MODEL_BINARY, S, false><<<nb, c->block(), 0, c->stream>>>(f, g, geo, r0, p0, c->partial());
     else if (c->pending)
-        k_stats_partial<Pol, MODEL_SINGLE, S, true><<<c->grid(), c->block(), 0, c->stream>>>(f, g, geo, r0, p0, c->partial());
+        k_stats_partial<Pol, MODEL_SINGLE, S, true><<<nb, c->block(), 0, c->stream>>>(f, g, geo, r0, p0, c->partial());
     else
-        k_stats_partial<Pol, MODEL_SINGLE, S, false><<<c->grid(), c->block(), 0, c->stream>>>(f, g, geo, r0, p0, c->partial());
-    k_stats_final<Pol><<<1, c->block(), 0, c->stream>>>(c->partial(), c->L.nblocks, out, bin ? 1 : 0);
+        k_stats_partial<Pol, MODEL_SINGLE, S, false><<<nb, c->block(), 0, c->stream>>>(f, g, geo, r0, p0, c->partial());
+    k_stats_final<Pol><<<1, c->block(), 0, c->stream>>>(c->partial(), nb, out, bin ? 1 : 0);
     return launch_status();
 }
 

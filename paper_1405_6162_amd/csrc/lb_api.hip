@@ -520,7 +520,7 @@ int lb_mask_index(lb_ctx* c, const uint8_t* mask, int32_t* index, int64_t* count
     if (!c || !mask || !index || !count) return LB_EINVAL;
     c->launched = true;
     const uint32_t n = (uint32_t)c->L.nsite;
-    const int nb = (int)((n + CB - 1) / CB);
+    const int nb = (int)((n + CB * CM - 1) / (CB * CM));
     int64_t* counts = reinterpret_cast<int64_t*>(c->partial());   // nb <= tiles of the launch grid
     Timed t(c, LB_K_OTHER);
     k_mask_count<<<nb, CB, 0, c->stream>>>(mask, n, counts);
