@@ -123,10 +123,11 @@ struct Geo {
 // blocks round-robin) sweeps a contiguous slab of tiles and the neighbouring
 // rows a pull or a stencil touches are in its own L2.  NTL / NTS select
 // nontemporal loads / stores of the distributions.
-template <int TX_, int TY_, int TZ_, bool NTL_, bool NTS_, bool XCD_>
+// WIDE: the distributions of 2- and 8-byte elements may be 4 GiB or larger.
+template <int TX_, int TY_, int TZ_, bool NTL_, bool NTS_, bool XCD_, bool WIDE_ = false>
 struct Tiling {
     static constexpr int TX = TX_, TY = TY_, TZ = TZ_, TPB = TX_ * TY_;
-    static constexpr bool nt_load = NTL_, nt_store = NTS_, xcd = XCD_;
+    static constexpr bool nt_load = NTL_, nt_store = NTS_, xcd = XCD_, wide = WIDE_;
     static_assert(TPB % 64 == 0, "whole wavefronts");
 };
 
@@ -240,9 +241,9 @@ __device__ __forceinline__ Site site_at(const Column& c, int v, const Geo& g) {
 // Global loads and stores of element `off` of an array whose base is the
 // same for the whole launch, nontemporal when the policy says so.  For 2-
 // and 8-byte elements the byte offset is formed in 32 bits (such arrays are
-// below 4 GiB here, checked on the host), so the address is a scalar base
-// plus a 32-bit vector offset and no 64-bit address arithmetic is spent per
-// lane.  4-byte elements take the element offset, scaled in 64 bits, so
+// below 4 GiB here, checked on the host, but for `wide` policies, below), so
+// the address is a scalar base plus a 32-bit vector offset and no 64-bit
+// address arithmetic is spent per lane.  4-byte elements take the element offset, scaled in 64 bits, so
 // that an FP32 state of up to 2^32 values keeps the blocked layout (384^3:
 // 4.3 GB, 7% faster than the structure of arrays it needed in bytes; no
 // difference at 256^3).  For 8-byte elements the 64-bit form was 0.6%
@@ -250,8 +251,9 @@ __device__ __forceinline__ Site site_at(const Column& c, int v, const Geo& g) {
 // elements once ran 20-30% slower in the 32-bit form, because a running sum
 // over 19 gathered values then sent its loads out one at a time; with the
 // values gathered into an array before the sum it is 1% faster for them.)
-// WIDE is the element form; the default is the one described above, and a
-// kernel that is launched apart for arrays below and beyond 4 GiB names it.
+// WIDE is the element form, which 2- and 8-byte elements take under a policy
+// with `wide` (wide_of): blocked distributions of 4 GiB and more.
+template <class P, class S> constexpr bool wide_of = sizeof(S) == 4 || P::wide;
 template <class S, bool WIDE = sizeof(S) == 4>
 __device__ __forceinline__ const S* at(const S* base, uint32_t off) {
     if constexpr (WIDE) return base + off;

@@ -90,13 +90,13 @@ struct FreeEnergy {
 
 // Load the 19 populations of one site (pulled from s - c_i when GATHER) from
 // direction arrays `stride` elements apart (default: the lattice's own).
-template <class P, bool GATHER, class S, class T, bool WIDE = sizeof(S) == 4>
+template <class P, bool GATHER, class S, class T>
 __device__ __forceinline__ void load_site(const S* src, const Site& st, const Geo& geo, T (&v)[Q],
                                           int64_t stride = -1) {
     const int64_t ds = stride < 0 ? geo.dstride : stride;
     static_for<0, Q>([&](auto I) {
         constexpr int i = decltype(I)::value;
-        v[i] = static_cast<T>(ldg<P::nt_load, S, WIDE>(src + i * ds, src_offset<i, GATHER>(st, geo)));
+        v[i] = static_cast<T>(ldg<P::nt_load, S, wide_of<P, S>>(src + i * ds, src_offset<i, GATHER>(st, geo)));
     });
 }
 
@@ -150,7 +150,7 @@ __global__ __launch_bounds__(P::TPB) void k_phi(const S* __restrict__ g, typenam
         A acc = A(0);
         static_for<0, Q>([&](auto I) {
             constexpr int i = decltype(I)::value;
-            acc = acc + static_cast<A>(static_cast<T>(ldg<P::nt_load>(g + i * geo.dstride, src_offset<i, GATHER>(st, geo))));
+            acc = acc + static_cast<A>(static_cast<T>(ldg<P::nt_load, S, wide_of<P, S>>(g + i * geo.dstride, src_offset<i, GATHER>(st, geo))));
         });
         phi[canon_at<0, 0, 0>(st, geo)] = static_cast<T>(static_cast<A>(phi0) + acc);
     }
@@ -287,7 +287,7 @@ __device__ __forceinline__ void relax_single(const T (&f)[Q], S* fdst, uint32_t 
     collide_single<COLL, S>(f, cp, [&](auto I, S v) { out[decltype(I)::value] = v; });
     static_for<0, Q>([&](auto I) {
         constexpr int i = decltype(I)::value;
-        stg<P::nt_store>(fdst + i * geo.dstride, off, out[i]);
+        stg<P::nt_store, S, wide_of<P, S>>(fdst + i * geo.dstride, off, out[i]);
     });
 }
 
@@ -385,8 +385,8 @@ __global__ __launch_bounds__(P::TPB) void k_collide(const S* fsrc, const S* gsrc
             const uint32_t off = offset_at<0, 0, 0>(st, geo);
             collide_binary<COLL, S>(
                 f, g, cp, sten,
-                [&](auto I, S v) { stg<P::nt_store>(fdst + decltype(I)::value * geo.dstride, off, v); },
-                [&](auto I, S v) { stg<P::nt_store>(gdst + decltype(I)::value * geo.dstride, off, v); });
+                [&](auto I, S v) { stg<P::nt_store, S, wide_of<P, S>>(fdst + decltype(I)::value * geo.dstride, off, v); },
+                [&](auto I, S v) { stg<P::nt_store, S, wide_of<P, S>>(gdst + decltype(I)::value * geo.dstride, off, v); });
         }
     } else {
 #pragma unroll
@@ -817,8 +817,8 @@ __global__ __launch_bounds__(P::TPB) void k_stream(const S* __restrict__ src, S*
         const uint32_t off = offset_at<0, 0, 0>(st, dgeo);
         static_for<0, Q>([&](auto I) {
             constexpr int i = decltype(I)::value;
-            stg<P::nt_store>(dst + i * dgeo.dstride, off,
-                             ldg<P::nt_load>(src + i * geo.dstride, src_offset<i, GATHER>(st, geo)));
+            stg<P::nt_store, S, wide_of<P, S>>(dst + i * dgeo.dstride, off,
+                             ldg<P::nt_load, S, wide_of<P, S>>(src + i * geo.dstride, src_offset<i, GATHER>(st, geo)));
         });
     }
 }
@@ -840,10 +840,10 @@ __global__ __launch_bounds__(P::TPB) void k_stream2(const S* __restrict__ fsrc, 
         static_for<0, Q>([&](auto I) {
             constexpr int i = decltype(I)::value;
             const uint32_t up = src_offset<i, GATHER>(st, geo);
-            const S fv = ldg<P::nt_load>(fsrc + i * geo.dstride, up);
-            const S gv = ldg<P::nt_load>(gsrc + i * geo.dstride, up);
-            stg<P::nt_store>(fdst + i * dgeo.dstride, off, fv);
-            stg<P::nt_store>(gdst + i * dgeo.dstride, off, gv);
+            const S fv = ldg<P::nt_load, S, wide_of<P, S>>(fsrc + i * geo.dstride, up);
+            const S gv = ldg<P::nt_load, S, wide_of<P, S>>(gsrc + i * geo.dstride, up);
+            stg<P::nt_store, S, wide_of<P, S>>(fdst + i * dgeo.dstride, off, fv);
+            stg<P::nt_store, S, wide_of<P, S>>(gdst + i * dgeo.dstride, off, gv);
         });
     }
 }
@@ -878,9 +878,9 @@ __global__ __launch_bounds__(P::TPB) void k_init(const double* __restrict__ rho_
                 constexpr int i = decltype(I)::value;
                 const double cu = cdot<i>(ux, uy, uz);
                 const double base = 3.0 * cu + 4.5 * cu * cu - 1.5 * usq;
-                *at(f + i * geo.dstride, off) =
+                *at<S, wide_of<P, S>>(f + i * geo.dstride, off) =
                     static_cast<S>(weight<double>(i) * (drho + rho * base + fe.template stress_term<i>(cp)));
-                *at(g + i * geo.dstride, off) =
+                *at<S, wide_of<P, S>>(g + i * geo.dstride, off) =
                     static_cast<S>(weight<double>(i) * (dphi + p * base + fe.template mobility_term<i>(cp)));
             });
         } else {
@@ -888,7 +888,7 @@ __global__ __launch_bounds__(P::TPB) void k_init(const double* __restrict__ rho_
                 constexpr int i = decltype(I)::value;
                 const double cu = cdot<i>(ux, uy, uz);
                 const double base = 3.0 * cu + 4.5 * cu * cu - 1.5 * usq;
-                *at(f + i * geo.dstride, off) = static_cast<S>(weight<double>(i) * (drho + rho * base));
+                *at<S, wide_of<P, S>>(f + i * geo.dstride, off) = static_cast<S>(weight<double>(i) * (drho + rho * base));
             });
         }
     }
@@ -911,7 +911,7 @@ __global__ __launch_bounds__(P::TPB) void k_moments(const S* __restrict__ f, con
         double fv[Q];
         static_for<0, Q>([&](auto I) {
             constexpr int i = decltype(I)::value;
-            fv[i] = static_cast<double>(*at(f + i * geo.dstride, src_offset<i, GATHER>(st, geo)));
+            fv[i] = static_cast<double>(*at<S, wide_of<P, S>>(f + i * geo.dstride, src_offset<i, GATHER>(st, geo)));
         });
         double drho, jx, jy, jz;
         moments_of(fv, drho, jx, jy, jz);
@@ -927,7 +927,7 @@ __global__ __launch_bounds__(P::TPB) void k_moments(const S* __restrict__ f, con
                 double acc = 0.0;
                 static_for<0, Q>([&](auto I) {
                     constexpr int i = decltype(I)::value;
-                    acc = acc + static_cast<double>(*at(g + i * geo.dstride, src_offset<i, GATHER>(st, geo)));
+                    acc = acc + static_cast<double>(*at<S, wide_of<P, S>>(g + i * geo.dstride, src_offset<i, GATHER>(st, geo)));
                 });
                 phi_out[off] = phi0 + acc;
             }
@@ -1011,8 +1011,8 @@ __global__ __launch_bounds__(P::TPB) void k_sums_partial(const S* __restrict__ f
         S fv[Q], gv[MODEL == MODEL_BINARY ? Q : 1];      // all loads of a site go out as one batch
         static_for<0, Q>([&](auto I) {
             constexpr int i = decltype(I)::value;
-            fv[i] = *at(f + i * geo.dstride, off);
-            if constexpr (MODEL == MODEL_BINARY) gv[i] = *at(g + i * geo.dstride, off);
+            fv[i] = *at<S, wide_of<P, S>>(f + i * geo.dstride, off);
+            if constexpr (MODEL == MODEL_BINARY) gv[i] = *at<S, wide_of<P, S>>(g + i * geo.dstride, off);
         });
         static_for<0, Q>([&](auto I) {
             constexpr int i = decltype(I)::value;
@@ -1079,13 +1079,13 @@ __global__ __launch_bounds__(P::TPB) void k_stats_partial(const S* __restrict__ 
         double fv[Q];
         static_for<0, Q>([&](auto I) {
             constexpr int i = decltype(I)::value;
-            fv[i] = static_cast<double>(*at(f + i * geo.dstride, src_offset<i, GATHER>(st, geo)));
+            fv[i] = static_cast<double>(*at<S, wide_of<P, S>>(f + i * geo.dstride, src_offset<i, GATHER>(st, geo)));
         });
         double gv[MODEL == MODEL_BINARY ? Q : 1];
         if constexpr (MODEL == MODEL_BINARY) {
             static_for<0, Q>([&](auto I) {
                 constexpr int i = decltype(I)::value;
-                gv[i] = static_cast<double>(*at(g + i * geo.dstride, src_offset<i, GATHER>(st, geo)));
+                gv[i] = static_cast<double>(*at<S, wide_of<P, S>>(g + i * geo.dstride, src_offset<i, GATHER>(st, geo)));
             });
         }
         double drho, jx, jy, jz;
@@ -1852,7 +1852,7 @@ __global__ __launch_bounds__(CB) void k_get_sites(const S* __restrict__ buf, con
     const Site st = site_of_index(s, geo);
     static_for<0, Q>([&](auto I) {
         constexpr int i = decltype(I)::value;
-        packed[i * m + t] = *at(buf + i * geo.dstride, src_offset<i, PENDING>(st, geo));
+        packed[i * m + t] = buf[i * geo.dstride + src_offset<i, PENDING>(st, geo)];
     });
 }
 
@@ -1868,7 +1868,7 @@ __global__ __launch_bounds__(CB) void k_set_sites(S* __restrict__ buf, const int
     const Site st = site_of_index(s, geo);
     static_for<0, Q>([&](auto I) {
         constexpr int i = decltype(I)::value;
-        *at(buf + i * geo.dstride, src_offset<i, PENDING>(st, geo)) = packed[i * m + t];
+        buf[i * geo.dstride + src_offset<i, PENDING>(st, geo)] = packed[i * m + t];
     });
 }
 

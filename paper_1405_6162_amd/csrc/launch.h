@@ -34,6 +34,8 @@ using Pol = Tiling<64, 4, 1, false, true, true>;
 // single fluid in pairs FP32 96^3 15.6 / 19.7, 112^3 22.9 / 30.0; beyond the
 // cache they lose: FP64 128^3 261 / 247, 256^3 1919 / 1819.
 template <class P> using Cached = Tiling<P::TX, P::TY, P::TZ, P::nt_load, false, P::xcd>;
+// The same for blocked states of 4 GiB and more a buffer (layout_of).
+template <class P> using Wide = Tiling<P::TX, P::TY, P::TZ, P::nt_load, P::nt_store, P::xcd, true>;
 constexpr size_t kCachedBytes = 280000000;
 // Pol with 2 and 4 sites per lane along z (lb_params.vvl).
 using Pol2 = Tiling<64, 4, 2, false, true, true>;
@@ -91,6 +93,7 @@ struct Layout {
     int64_t nsite;
     int64_t dstride;        // elements between consecutive directions
     bool blocked;           // 64-site blocks holding their 19 directions together
+    bool wide;              // blocked, with byte offsets beyond 32 bits
     uint32_t zs, ys, xbs;   // site-offset strides (Geo)
     size_t dist_bytes;      // one 19-direction buffer
     size_t phi_bytes;
@@ -130,31 +133,41 @@ inline Layout layout_of(const lb_params* p) {
     Layout L{};
     L.nsite = (int64_t)p->nx * p->ny * p->nz;
     const size_t es = storage_size(p->storage);
-    // Blocked layout (see Geo) whenever a buffer's offsets fit in 32 bits
-    // (in bytes; for 4-byte elements, which are addressed by element, in
-    // elements);
+    // Blocked layout (see Geo) whenever a buffer's offsets fit in 32 bits (in
+    // bytes; for 4-byte elements, which are addressed by element, in elements);
     // the last x block of a row is padded to 64 sites.  Measured A/B on one
     // box against the structure-of-arrays layout: the single-fluid step
     // +4.6% (FP64) and +5.6% (FP32) at 256^3, the binary march +4.3% (FP64,
     // 256^3), +3.0% (FP64, 128^3), +3.6% (FP16, 384^3) and +2.5 to +5.6%
     // (FP32, 128^3 to 256^3); padding between the buffers changed none of
     // these.
+    // From 4 GiB a buffer up, where the blocks need no more room than the
+    // structure of arrays (a lattice that fitted still does), the kernels take
+    // offsets by element (Wide) and the marching ones, whose bases are per
+    // plane, are as below 4 GiB: FP64 320^3 us a step, blocked / structure of
+    // arrays, 3793 / 4050 binary.  A state with more than one site per lane
+    // keeps the arrays, as do planes of 4 GiB (PlaneBase).
     const uint64_t xblocks = (uint64_t)tiles(p->nx, 64);
     const uint64_t blocked_elems = (uint64_t)p->nz * (uint64_t)p->ny * xblocks * Q * 64;
-    L.blocked = (es == 4 ? blocked_elems : blocked_elems * es) < ((uint64_t)1 << 32);
+    const size_t stride_bytes = round_up((size_t)L.nsite * es, kAlign) + kDirPadBytes;
+    const size_t soa_bytes = round_up(stride_bytes * Q, kAlign);
+    const uint64_t u32 = (uint64_t)1 << 32;
+    const bool small_plane = blocked_elems / (uint64_t)p->nz * es < u32;   // PlaneBase's offsets
+    L.blocked = small_plane && (es == 4 ? blocked_elems : blocked_elems * es) < u32;
+    if (!L.blocked && small_plane && es != 4 && p->vvl <= 1)
+        L.blocked = L.wide = blocked_elems < u32 && blocked_elems * es <= soa_bytes;
     if (L.blocked) {
         L.dstride = 64;
         L.xbs = Q * 64;
         L.ys = (uint32_t)(xblocks * L.xbs);
         L.zs = (uint32_t)((uint64_t)p->ny * L.ys);
-        L.dist_bytes = round_up((size_t)blocked_elems * es, kAlign);
+        L.dist_bytes = L.wide ? soa_bytes : round_up((size_t)blocked_elems * es, kAlign);
     } else {
-        const size_t stride_bytes = round_up((size_t)L.nsite * es, kAlign) + kDirPadBytes;
         L.dstride = (int64_t)(stride_bytes / es);
         L.xbs = 64;
         L.ys = (uint32_t)p->nx;
         L.zs = (uint32_t)p->nx * (uint32_t)p->ny;
-        L.dist_bytes = round_up(stride_bytes * Q, kAlign);
+        L.dist_bytes = soa_bytes;
     }
     L.phi_bytes = round_up((size_t)L.nsite * compute_size(p->storage), kAlign);
     L.nblocks = tiles(p->nx, Pol::TX) * tiles(p->ny, Pol::TY) * tiles(p->nz, Pol::TZ);
@@ -321,11 +334,18 @@ CollParams<typename Compute<S>::T> coll_params(const lb_ctx* c) {
 template <class F>
 int by_vvl(const lb_ctx* c, F&& fn) {
     switch (c->p.vvl) {
-        case 0: case 1: return c->cached() ? fn(Cached<Pol>{}) : fn(Pol{});
+        case 0: case 1: return c->L.wide ? fn(Wide<Pol>{}) : (c->cached() ? fn(Cached<Pol>{}) : fn(Pol{}));
         case 2: return fn(Pol2{});
         case 4: return fn(Pol4{});
     }
     return LB_EINVAL;
+}
+
+// Calls fn with the policy of a kernel that has one site per lane and stores
+// no distributions.
+template <class F>
+int by_width(const lb_ctx* c, F&& fn) {
+    return c->L.wide ? fn(Wide<Pol>{}) : fn(Pol{});
 }
 
 template <class S>
@@ -476,7 +496,7 @@ int run_copy(lb_ctx* c, const S* fs, const S* gs, S* fd, S* gd, const Geo& sgeo,
             k_stream<P, S, GATHER><<<c->grid(), c->block(), 0, c->stream>>>(fs, fd, sgeo, dgeo);
         return launch_status();
     };
-    return c->cached() ? with(Cached<Pol>{}) : with(Pol{});
+    return c->L.wide ? with(Wide<Pol>{}) : (c->cached() ? with(Cached<Pol>{}) : with(Pol{}));
 }
 
 // Materialise propagate(buffer[src]) into (f, g) of layout dgeo.
@@ -534,11 +554,10 @@ int launch_single_pair(lb_ctx* c, bool pending, const S* src, S* mid, S* dst, bo
 }
 
 // Whether two single-fluid steps run as one launch: not with more than one
-// site per lane (lb_params.vvl), nor on lattices too small or too large for
-// the blocked layout.
+// site per lane (lb_params.vvl), nor on lattices too small.
 template <class S>
 bool pair_pays(const lb_ctx* c) {
-    if (c->p.model != LB_SINGLE || c->p.vvl > 1 || !c->L.blocked || c->L.nsite < kPairMinSites<S>) return false;
+    if (c->p.model != LB_SINGLE || c->p.vvl > 1 || c->L.nsite < kPairMinSites<S>) return false;
     return sizeof(S) > 2 || (c->p.nx % PairTile::TX == 0 && c->p.ny % PairTile::TY == 0);
 }
 
@@ -546,8 +565,10 @@ template <class S>
 int run_step(lb_ctx* c, int32_t n) {
     if (pair_pays<S>(c)) {
         for (; n >= 2; n -= 2) {
-            const int rc = launch_single_pair<S, true, false>(c, c->pending, (const S*)c->fbuf(c->cur), nullptr,
-                                                              (S*)c->fbuf(1 - c->cur), false);
+            const S* src = (const S*)c->fbuf(c->cur);
+            S* dst = (S*)c->fbuf(1 - c->cur);
+            const int rc = c->L.blocked ? launch_single_pair<S, true, false>(c, c->pending, src, nullptr, dst, false)
+                                        : launch_single_pair<S, false, false>(c, c->pending, src, nullptr, dst, false);
             if (rc) return rc;
             c->cur = 1 - c->cur;
             c->pending = true;
@@ -572,9 +593,12 @@ int run_init(lb_ctx* c, const double* rho, const double* u, const double* phi) {
     cp.phi0 = c->p.storage == LB_F64 ? 0.0 : c->p.phi0;
     S* f = (S*)c->fbuf(c->cur);
     S* g = (S*)c->gbuf(c->cur);
-    if (c->p.model == LB_BINARY) k_init<Pol, MODEL_BINARY, S><<<c->grid(), c->block(), 0, c->stream>>>(rho, u, phi, f, g, c->geo(), cp);
-    else k_init<Pol, MODEL_SINGLE, S><<<c->grid(), c->block(), 0, c->stream>>>(rho, u, phi, f, g, c->geo(), cp);
-    int rc = launch_status();
+    const int rc = by_width(c, [&](auto pol) {
+        using P = decltype(pol);
+        if (c->p.model == LB_BINARY) k_init<P, MODEL_BINARY, S><<<c->grid(), c->block(), 0, c->stream>>>(rho, u, phi, f, g, c->geo(), cp);
+        else k_init<P, MODEL_SINGLE, S><<<c->grid(), c->block(), 0, c->stream>>>(rho, u, phi, f, g, c->geo(), cp);
+        return launch_status();
+    });
     if (rc == LB_OK) c->pending = false;
     return rc;
 }
@@ -587,14 +611,17 @@ int run_moments(lb_ctx* c, double* rho, double* u, double* phi) {
     const S* f = (const S*)c->fbuf(c->cur);
     const S* g = (const S*)c->gbuf(c->cur);
     const dim3 grid = c->grid(), block = c->block();
-    if (c->p.model == LB_BINARY) {
-        if (c->pending) k_moments<Pol, MODEL_BINARY, S, true><<<grid, block, 0, c->stream>>>(f, g, rho, u, phi, c->geo(), r0, p0);
-        else k_moments<Pol, MODEL_BINARY, S, false><<<grid, block, 0, c->stream>>>(f, g, rho, u, phi, c->geo(), r0, p0);
-    } else {
-        if (c->pending) k_moments<Pol, MODEL_SINGLE, S, true><<<grid, block, 0, c->stream>>>(f, g, rho, u, nullptr, c->geo(), r0, p0);
-        else k_moments<Pol, MODEL_SINGLE, S, false><<<grid, block, 0, c->stream>>>(f, g, rho, u, nullptr, c->geo(), r0, p0);
-    }
-    return launch_status();
+    return by_width(c, [&](auto pol) {
+        using P = decltype(pol);
+        if (c->p.model == LB_BINARY) {
+            if (c->pending) k_moments<P, MODEL_BINARY, S, true><<<grid, block, 0, c->stream>>>(f, g, rho, u, phi, c->geo(), r0, p0);
+            else k_moments<P, MODEL_BINARY, S, false><<<grid, block, 0, c->stream>>>(f, g, rho, u, phi, c->geo(), r0, p0);
+        } else {
+            if (c->pending) k_moments<P, MODEL_SINGLE, S, true><<<grid, block, 0, c->stream>>>(f, g, rho, u, nullptr, c->geo(), r0, p0);
+            else k_moments<P, MODEL_SINGLE, S, false><<<grid, block, 0, c->stream>>>(f, g, rho, u, nullptr, c->geo(), r0, p0);
+        }
+        return launch_status();
+    });
 }
 
 // Blocks of a reduction over the lattice: eight 256-lane ones a CU.
@@ -602,12 +629,12 @@ constexpr int kReduceBlocks = 8 * kCUs;
 
 // Sums of a state (f, g) in geo's layout into out, by way of `partial`; b0 and
 // b4 are added to sum rho and sum phi.
-template <class S>
+template <class S, class P = Pol>
 int sums_of(int model, const S* f, const S* g, const Geo& geo, double* partial, double b0, double b4, double* out,
             hipStream_t s) {
     const int nb = std::min(geo.nblocks, kReduceBlocks);
-    if (model == LB_BINARY) k_sums_partial<Pol, MODEL_BINARY, S><<<nb, Pol::TPB, 0, s>>>(f, g, geo, partial);
-    else k_sums_partial<Pol, MODEL_SINGLE, S><<<nb, Pol::TPB, 0, s>>>(f, nullptr, geo, partial);
+    if (model == LB_BINARY) k_sums_partial<P, MODEL_BINARY, S><<<nb, P::TPB, 0, s>>>(f, g, geo, partial);
+    else k_sums_partial<P, MODEL_SINGLE, S><<<nb, P::TPB, 0, s>>>(f, nullptr, geo, partial);
     k_sums_final<Pol, 5><<<1, Pol::TPB, 0, s>>>(partial, nb, out, b0, b4, 0);
     return launch_status();
 }
@@ -619,8 +646,10 @@ int run_sums(lb_ctx* c, double* out) {
     const double n = (double)c->L.nsite;
     const double b0 = dev ? n * c->p.rho0 : 0.0;
     const double b4 = (dev && c->p.model == LB_BINARY) ? n * c->p.phi0 : 0.0;
-    return sums_of<S>(c->p.model, (const S*)c->fbuf(c->cur), (const S*)c->gbuf(c->cur), c->geo(), c->partial(), b0,
-                      b4, out, c->stream);
+    return by_width(c, [&](auto pol) {
+        return sums_of<S, decltype(pol)>(c->p.model, (const S*)c->fbuf(c->cur), (const S*)c->gbuf(c->cur), c->geo(),
+                                         c->partial(), b0, b4, out, c->stream);
+    });
 }
 
 template <class S>
@@ -633,14 +662,18 @@ int run_stats(lb_ctx* c, double* out) {
     const Geo geo = c->geo();
     const bool bin = c->p.model == LB_BINARY;
     const int nb = std::min(c->L.nblocks, kReduceBlocks);
-    if (bin && c->pending)
-        k_stats_partial<Pol, MODEL_BINARY, S, true><<<nb, c->block(), 0, c->stream>>>(f, g, geo, r0, p0, c->partial());
-    else if (bin)
-        k_stats_partial<Pol, MODEL_BINARY, S, false><<<nb, c->block(), 0, c->stream>>>(f, g, geo, r0, p0, c->partial());
-    else if (c->pending)
-        k_stats_partial<Pol, MODEL_SINGLE, S, true><<<nb, c->block(), 0, c->stream>>>(f, g, geo, r0, p0, c->partial());
-    else
-        k_stats_partial<Pol, MODEL_SINGLE, S, false><<<nb, c->block(), 0, c->stream>>>(f, g, geo, r0, p0, c->partial());
+    by_width(c, [&](auto pol) {
+        using P = decltype(pol);
+        if (bin && c->pending)
+            k_stats_partial<P, MODEL_BINARY, S, true><<<nb, c->block(), 0, c->stream>>>(f, g, geo, r0, p0, c->partial());
+        else if (bin)
+            k_stats_partial<P, MODEL_BINARY, S, false><<<nb, c->block(), 0, c->stream>>>(f, g, geo, r0, p0, c->partial());
+        else if (c->pending)
+            k_stats_partial<P, MODEL_SINGLE, S, true><<<nb, c->block(), 0, c->stream>>>(f, g, geo, r0, p0, c->partial());
+        else
+            k_stats_partial<P, MODEL_SINGLE, S, false><<<nb, c->block(), 0, c->stream>>>(f, g, geo, r0, p0, c->partial());
+        return 0;
+    });
     k_stats_final<Pol><<<1, c->block(), 0, c->stream>>>(c->partial(), nb, out, bin ? 1 : 0);
     return launch_status();
 }
@@ -662,11 +695,11 @@ int run_set_state(lb_ctx* c, const S* f, const S* g) {
     return LB_OK;
 }
 
-// nsteps single-fluid steps whose post-collision fields go to post[k] (canonical
-// stride N); afterwards the state is pending on a copy of the last of them.
-// Binary: step k writes post-collision f then g at post + k*38*N.  Step 0
-// collides the context's state in its own buffers and copies the result out;
-// later steps march from post[k-1] to post[k] (both of direction stride N).
+// nsteps binary steps whose post-collision fields go to canonical memory, f
+// then g of step k to post + k*38*N; afterwards the state is pending on a copy
+// of the last of them.  Step 0 collides the context's state in its own buffers
+// and copies the result out; later steps march from post[k-1] to post[k] (both
+// of direction stride N).
 template <class S>
 int run_step_record_binary(lb_ctx* c, int32_t n, S* post, typename Compute<S>::T* phi) {
     using T = typename Compute<S>::T;
@@ -675,8 +708,12 @@ int run_step_record_binary(lb_ctx* c, int32_t n, S* post, typename Compute<S>::T
     if (phi) {                                        // phi of the state step 0 collides
         Timed t(c, LB_K_PHI);
         const S* g = (const S*)c->gbuf(c->cur);
-        if (c->pending) k_phi<Pol, S, true><<<c->grid(), c->block(), 0, c->stream>>>(g, phi, c->geo(), cp.phi0);
-        else k_phi<Pol, S, false><<<c->grid(), c->block(), 0, c->stream>>>(g, phi, c->geo(), cp.phi0);
+        by_width(c, [&](auto pol) {
+            using P = decltype(pol);
+            if (c->pending) k_phi<P, S, true><<<c->grid(), c->block(), 0, c->stream>>>(g, phi, c->geo(), cp.phi0);
+            else k_phi<P, S, false><<<c->grid(), c->block(), 0, c->stream>>>(g, phi, c->geo(), cp.phi0);
+            return 0;
+        });
     }
     int rc = run_collide<S>(c);                       // state now direct: the post-collision field
     if (rc) return rc;
@@ -731,39 +768,45 @@ int run_step_record_binary(lb_ctx* c, int32_t n, S* post, typename Compute<S>::T
     return LB_OK;
 }
 
+// The same for the single fluid, 19 N values a step: step 0 goes from the
+// context's state to post[0]; the rest run in pairs where a pair beats two steps
+// (the first one's values are stored too: 64^3 31.3 us a pair, 36.0 us two
+// steps).
 template <class S>
 int run_step_record(lb_ctx* c, int32_t n, S* post, typename Compute<S>::T* phi) {
     if (c->p.model == LB_BINARY) return run_step_record_binary<S>(c, n, post, phi);
     const int64_t N = c->L.nsite;
     const auto cp = coll_params<S>(c);
-    const dim3 grid = c->grid(), block = c->block();
-    // one collision from src (layout sg; pull from a pending src when GATHER)
-    // into canonical dst, for the context's collision
+    // one collision from src (layout sg; pull from a pending src when `gather`)
+    // into canonical dst
     const Geo cg = c->canonical_geo();
-    auto collide = [&](auto gather, const S* src, const Geo& sg, S* dst) {
-        constexpr bool G = decltype(gather)::value;
-        if (c->p.collision == LB_TRT)
-            k_collide_single_strided<Pol, S, G, COLL_TRT><<<grid, block, 0, c->stream>>>(src, dst, sg, cg, cp);
-        else if (c->p.collision == LB_MRT)
-            k_collide_single_strided<Pol, S, G, COLL_MRT><<<grid, block, 0, c->stream>>>(src, dst, sg, cg, cp);
-        else
-            k_collide_single_strided<Pol, S, G><<<grid, block, 0, c->stream>>>(src, dst, sg, cg, cp);
+    auto collide = [&](bool gather, const S* src, const Geo& sg, S* dst) {
+        Timed t(c, LB_K_COLLIDE);
+        return by_width(c, [&](auto pol) {
+            using P = decltype(pol);
+            const dim3 grid = c->grid(), block = c->block();
+            by_collision(c, [&](auto coll) {
+                constexpr int COLL = decltype(coll)::value;
+                if (gather) k_collide_single_strided<P, S, true, COLL><<<grid, block, 0, c->stream>>>(src, dst, sg, cg, cp);
+                else k_collide_single_strided<P, S, false, COLL><<<grid, block, 0, c->stream>>>(src, dst, sg, cg, cp);
+            });
+            return launch_status();
+        });
     };
-    for (int32_t k = 0; k < n; ++k) {
+    int err = collide(c->pending, (const S*)c->fbuf(c->cur), c->geo(), post);
+    const bool pairs = pair_pays<S>(c);
+    for (int32_t k = 1; k < n && err == LB_OK;) {
+        const S* src = post + (size_t)(k - 1) * Q * N;
         S* dst = post + (size_t)k * Q * N;
-        {
-            Timed t(c, LB_K_COLLIDE);
-            if (k == 0) {
-                const S* src = (const S*)c->fbuf(c->cur);
-                if (c->pending) collide(std::true_type{}, src, c->geo(), dst);
-                else collide(std::false_type{}, src, c->geo(), dst);
-            } else {
-                collide(std::true_type{}, post + (size_t)(k - 1) * Q * N, cg, dst);
-            }
+        if (pairs && k + 1 < n) {
+            err = launch_single_pair<S, false, true>(c, true, src, dst, dst + Q * N, true);
+            k += 2;
+        } else {
+            err = collide(true, src, cg, dst);
+            k += 1;
         }
-        int rc = launch_status();
-        if (rc) return rc;
     }
+    if (err) return err;
     Timed t(c, LB_K_OTHER);
     const int rc = run_convert<S>(c, post + (size_t)(n - 1) * Q * N, nullptr, (S*)c->fbuf(c->cur), nullptr, cg,
                                   c->geo());

@@ -77,3 +77,27 @@ def test_pairs_against_oracle(lbgpu):
     f = lat.get_state()[0].cpu().numpy()
     lat.close()
     assert np.abs(f - want).max() <= 1e-12 * np.abs(want).max()
+
+
+@pytest.mark.parametrize("coll", ["bgk", "trt", "mrt"])
+@pytest.mark.parametrize("storage,nx,ny,nz", [("f64", 67, 9, 216), ("f64", 64, 64, 32), ("f32", 129, 40, 41),
+                                              ("f16", 128, 128, 123)])
+def test_recorded_pairs_equal_single_steps(lbgpu, storage, nx, ny, nz, coll):
+    """lb_step_record pairs its steps from the second one on; every recorded
+    post-collision field has the bits of collide and propagate calls."""
+    print("case record single %dx%dx%d %s %s" % (nx, ny, nz, storage, coll), flush=True)
+    code = {"f64": lbgpu.LB_F64, "f32": lbgpu.LB_F32, "f16": lbgpu.LB_F16}[storage]
+    rho, u = _fields(nx, ny, nz)
+    a, b = (lbgpu.Lattice(nx, ny, nz, storage=code, tau_f=0.8, **COLL[coll]) for _ in range(2))
+    for lat in (a, b):
+        lat.init_equilibrium(rho, u)
+    for n in (1, 2, 3, 4, 5):            # the first from a direct state, the others from a pending one
+        post = torch.full((n, 19, nz, ny, nx), float("nan"), dtype=lbgpu.STORAGE_DTYPE[code], device="cuda")
+        lbgpu.lb_step_record(a.ctx, n, post)
+        for k in range(n):
+            b.collide()
+            assert torch.equal(post[k], b.get_state()[0])
+            b.propagate()
+        assert torch.equal(a.get_state()[0], b.get_state()[0])
+    a.close()
+    b.close()
