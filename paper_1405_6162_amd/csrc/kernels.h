@@ -347,7 +347,8 @@ __device__ __forceinline__ void collide_binary(const T (&f)[Q], const T (&g)[Q],
     if constexpr (COLL != COLL_BGK) relax_parts<COLL, S>(f, neq, cp, put_f);
 }
 
-template <class P, int MODEL, class S, bool GATHER, int COLL = COLL_BGK>
+// CANON: the destination (binary) is canonical, whatever the source's layout.
+template <class P, int MODEL, class S, bool GATHER, int COLL = COLL_BGK, bool CANON = false>
 __global__ __launch_bounds__(P::TPB) void k_collide(const S* fsrc, const S* gsrc, S* fdst, S* gdst,
                                                     const typename Compute<S>::T* __restrict__ phi, Geo geo,
                                                     CollParams<typename Compute<S>::T> cp) {
@@ -382,11 +383,12 @@ __global__ __launch_bounds__(P::TPB) void k_collide(const S* fsrc, const S* gsrc
             T f[Q], g[Q];
             load_site<P, GATHER>(fsrc, st, geo, f);
             load_site<P, GATHER>(gsrc, st, geo, g);
-            const uint32_t off = offset_at<0, 0, 0>(st, geo);
+            const uint32_t off = CANON ? canon_at<0, 0, 0>(st, geo) : offset_at<0, 0, 0>(st, geo);
+            const int64_t ds = CANON ? (int64_t)geo.nsite : geo.dstride;
             collide_binary<COLL, S>(
                 f, g, cp, sten,
-                [&](auto I, S v) { stg<P::nt_store, S, wide_of<P, S>>(fdst + decltype(I)::value * geo.dstride, off, v); },
-                [&](auto I, S v) { stg<P::nt_store, S, wide_of<P, S>>(gdst + decltype(I)::value * geo.dstride, off, v); });
+                [&](auto I, S v) { stg<P::nt_store, S, wide_of<P, S>>(fdst + decltype(I)::value * ds, off, v); },
+                [&](auto I, S v) { stg<P::nt_store, S, wide_of<P, S>>(gdst + decltype(I)::value * ds, off, v); });
         }
     } else {
 #pragma unroll
@@ -1412,6 +1414,18 @@ __device__ __forceinline__ T* dir_at(T* base, int i, int64_t dstride, uint32_t o
     else return at(base + i * dstride, o);
 }
 
+// Loads of values read once (the states) and stores of the adjoints:
+// nontemporal under a policy with nontemporal stores.
+template <class P>
+__device__ __forceinline__ double get(const double* p) {
+    return P::nt_store ? __builtin_nontemporal_load(p) : *p;
+}
+template <class P>
+__device__ __forceinline__ void put(double* p, double v) {
+    if constexpr (P::nt_store) __builtin_nontemporal_store(v, p);
+    else *p = v;
+}
+
 // How the local kernel obtains the post-collision g adjoints of its site,
 // lambda*_j(s) = lambda_g^{n+1}_j(s + c_j), and whether it keeps them:
 //   LG_GATHER       gathered from lambda_g^{n+1} (canonical);
@@ -1491,7 +1505,7 @@ __global__ __launch_bounds__(P::TPB, 2) void k_adjoint_binary(const double* __re
         double mf[MRT ? 7 : 1] = {};                    // MRT: f on the seven extra moments
         static_for<0, Q>([&](auto I) {
             constexpr int i = decltype(I)::value;
-            const double fi = *dir_at<OFF32>(fn, i, geo.dstride, src_offset<i, F_PENDING>(st, geo));
+            const double fi = get<P>(dir_at<OFF32>(fn, i, geo.dstride, src_offset<i, F_PENDING>(st, geo)));
             double li;
             if constexpr (MRT) {
                 static_for<0, 7>([&](auto Kx) {
@@ -1525,11 +1539,11 @@ __global__ __launch_bounds__(P::TPB, 2) void k_adjoint_binary(const double* __re
         double dwg = 0.0;
         static_for<0, Q>([&](auto I) {
             constexpr int i = decltype(I)::value;
-            const double gi = *dir_at<OFF32>(gn, i, geo.dstride, src_offset<i, F_PENDING>(st, geo));
+            const double gi = get<P>(dir_at<OFF32>(gn, i, geo.dstride, src_offset<i, F_PENDING>(st, geo)));
             const uint32_t up = offset_at<cx(i), cy(i), cz(i)>(st, geo);
             double l = *dir_at<OFF32>(lg_next, i, geo.dstride, up);
             if constexpr (LG == LG_PULLED_KEEP) l = (1.0 - cp.omega_g) * l + *at(b_next, up);
-            if constexpr (LG != LG_GATHER) *dir_at<OFF32>(p_out, i, geo.dstride, off) = l;
+            if constexpr (LG != LG_GATHER) put<P>(dir_at<OFF32>(p_out, i, geo.dstride, off), l);
             const double cu = cdot<i>(ux, uy, uz);
             const double E = 1.0 + 3.0 * cu + 4.5 * cu * cu - 1.5 * usq;
             gs.template add<i>(l, cu, E, 0.0);
@@ -1596,9 +1610,10 @@ __global__ __launch_bounds__(P::TPB, 2) void k_adjoint_binary(const double* __re
         static_for<0, Q>([&](auto I) {
             constexpr int i = decltype(I)::value;
             if constexpr (SPLIT) {
-                *dir_at<OFF32>(lf_n, i, geo.dstride, off) = lf[i][t] - mu_at(I) + base + cdot<i>(V[0], V[1], V[2]);
+                put<P>(dir_at<OFF32>(lf_n, i, geo.dstride, off), lf[i][t] - mu_at(I) + base + cdot<i>(V[0], V[1], V[2]));
             } else {
-                *dir_at<OFF32>(lf_n, i, geo.dstride, off) = (1.0 - cp.omega_f) * lf[i][t] + base + cdot<i>(V[0], V[1], V[2]);
+                put<P>(dir_at<OFF32>(lf_n, i, geo.dstride, off),
+                       (1.0 - cp.omega_f) * lf[i][t] + base + cdot<i>(V[0], V[1], V[2]));
             }
         });
         afield[off] = r.a_phi;

@@ -697,33 +697,37 @@ int run_set_state(lb_ctx* c, const S* f, const S* g) {
 
 // nsteps binary steps whose post-collision fields go to canonical memory, f
 // then g of step k to post + k*38*N; afterwards the state is pending on a copy
-// of the last of them.  Step 0 collides the context's state in its own buffers
-// and copies the result out; later steps march from post[k-1] to post[k] (both
-// of direction stride N).
+// of the last of them.  Step 0 collides the context's state into post[0] (128^3:
+// 360 us with its phi; in the context's buffers and copied out it was 600);
+// later steps march from post[k-1] to post[k] (both of direction stride N).
 template <class S>
 int run_step_record_binary(lb_ctx* c, int32_t n, S* post, typename Compute<S>::T* phi) {
     using T = typename Compute<S>::T;
     const int64_t N = c->L.nsite;
     const auto cp = coll_params<S>(c);
-    if (phi) {                                        // phi of the state step 0 collides
-        Timed t(c, LB_K_PHI);
+    int rc = by_width(c, [&](auto pol) {              // step 0: phi of the state, then its collision
+        using P = decltype(pol);
+        const S* f = (const S*)c->fbuf(c->cur);
         const S* g = (const S*)c->gbuf(c->cur);
-        by_width(c, [&](auto pol) {
-            using P = decltype(pol);
-            if (c->pending) k_phi<P, S, true><<<c->grid(), c->block(), 0, c->stream>>>(g, phi, c->geo(), cp.phi0);
-            else k_phi<P, S, false><<<c->grid(), c->block(), 0, c->stream>>>(g, phi, c->geo(), cp.phi0);
-            return 0;
+        T* ph = phi ? phi : (T*)c->phi();
+        {
+            Timed t(c, LB_K_PHI);
+            if (c->pending) k_phi<P, S, true><<<c->grid(), c->block(), 0, c->stream>>>(g, ph, c->geo(), cp.phi0);
+            else k_phi<P, S, false><<<c->grid(), c->block(), 0, c->stream>>>(g, ph, c->geo(), cp.phi0);
+        }
+        Timed t(c, LB_K_COLLIDE);
+        by_collision(c, [&](auto coll) {
+            constexpr int COLL = decltype(coll)::value;
+            if (c->pending)
+                k_collide<P, MODEL_BINARY, S, true, COLL, true><<<c->grid(), c->block(), 0, c->stream>>>(
+                    f, g, post, post + Q * N, ph, c->geo(), cp);
+            else
+                k_collide<P, MODEL_BINARY, S, false, COLL, true><<<c->grid(), c->block(), 0, c->stream>>>(
+                    f, g, post, post + Q * N, ph, c->geo(), cp);
         });
-    }
-    int rc = run_collide<S>(c);                       // state now direct: the post-collision field
+        return launch_status();
+    });
     if (rc) return rc;
-    {
-        Timed t(c, LB_K_OTHER);
-        rc = run_convert<S>(c, (const S*)c->fbuf(c->cur), (const S*)c->gbuf(c->cur), post, post + Q * N, c->geo(),
-                            c->canonical_geo());
-        if (rc) return rc;
-    }
-    c->pending = true;
     const bool march = march_pays<S>(c);
     Geo cg = c->canonical_geo();
     for (int32_t k = 1; k < n; ++k) {
@@ -758,13 +762,14 @@ int run_step_record_binary(lb_ctx* c, int32_t n, S* post, typename Compute<S>::T
             rc = launch_march<S, false, false>(c, src, src + Q * N, dst, dst + Q * N, true, nullptr);
         if (rc) return rc;
     }
-    if (n > 1) {
+    {
         Timed t(c, LB_K_OTHER);
         const S* last = post + (size_t)(n - 1) * 2 * Q * N;
         rc = run_convert<S>(c, last, last + Q * N, (S*)c->fbuf(c->cur), (S*)c->gbuf(c->cur), c->canonical_geo(),
                             c->geo());
         if (rc) return rc;
     }
+    c->pending = true;
     return LB_OK;
 }
 
