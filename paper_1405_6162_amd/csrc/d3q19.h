@@ -159,11 +159,12 @@ __device__ __forceinline__ int tile_index(const Geo& g) {
 }
 
 // Tile and chunk of planes of a marching kernel's block; false for the
-// surplus blocks of a grid rounded up to a multiple of 8: block b takes tile
-// (b mod 8) * grid/8 + b/8, so each XCD sweeps a contiguous run of tiles for
-// any count.  (Without the rounding 150 x 70 x 90, whose count is no multiple
-// of 8, lost its neighbours' lines in L2: a single-fluid FP32 pair took 51 us
-// there instead of 36.)  The geo.gz chunks split nz evenly.
+// surplus blocks of a grid rounded up.  In a grid that is a multiple of 8, block
+// b takes tile (b mod 8) * grid/8 + b/8, so each XCD sweeps a contiguous run of
+// tiles for any count.  (Without the rounding 150 x 70 x 90, whose count is no
+// multiple of 8, lost its neighbours' lines in L2: a single-fluid FP32 pair
+// took 51 us there instead of 36.)  In any other grid the order is the launch
+// order (march_grid says which it is).  The geo.gz chunks split nz evenly.
 //
 // A last column less than full leaves lanes idle.  Narrower tiles for it (32,
 // 16 and 8 wide, by the digits of what is left) were measured and are worse:
@@ -174,7 +175,8 @@ struct TileAt { int x0, y0, z0, z1; };
 
 template <class P>
 __device__ __forceinline__ bool tile_of_block(const Geo& g, TileAt& r) {
-    const int b = (int)((blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3));
+    int b = (int)blockIdx.x;
+    if ((gridDim.x & 7) == 0) b = (b & 7) * (int)(gridDim.x >> 3) + (b >> 3);
     if (b >= g.nblocks) return false;
     const int zc = b / (g.gx * g.gy);
     r.x0 = b % g.gx * P::TX;
