@@ -93,13 +93,11 @@ extern "C" {
  * marches each tile column through a chunk of z planes, computing phi and its
  * stencils on chip (608 B/site in FP64): fastest on large lattices.
  * LB_STEP_TWO_PASS: a phi pass, then the fused collide (776 B/site), every
- * site in parallel: fastest on small lattices, where the march has too few
- * blocks to hide its per-plane latency.  LB_STEP_AUTO (0, the default): the
- * march when its grid has at least 256 blocks (64 x 8 tiles; chunks of 64
- * planes where that gives more than 512 blocks, else as many chunks as fill 512
- * blocks, at most nz/16 of them; 128^3 has 256), else the
- * two-pass step.  (FP32 and FP16 march on 128 x 4 tiles where nx mod 128 is
- * 0 or above 64.) */
+ * site in parallel: fastest on small FP64 lattices, where the few blocks of
+ * the march each run their planes in sequence.  LB_STEP_AUTO (0, the
+ * default): with vvl 0 or 1 the march in LB_F32 and LB_F16 and, in LB_F64,
+ * from 200000 sites; with more sites per lane the march from 128^3 sites;
+ * else the two-pass step. */
 #define LB_STEP_AUTO     0
 #define LB_STEP_MARCH    1
 #define LB_STEP_TWO_PASS 2
@@ -186,14 +184,13 @@ int lb_propagate(lb_ctx* ctx);
 
 /* nsteps x (collide; propagate).  nsteps == 0 is a no-op, < 0 is LB_EINVAL.
  * Each step is one launch of a fused pull-stream + collide kernel.  For
- * LB_SINGLE with vvl 0 or 1, lattices from 130000 (LB_F64), 200000 (LB_F32) or
- * 2000000 (LB_F16, nx a multiple of 64 and ny of 8) sites take their steps two to a launch, the state between
- * them staying on chip (an odd last step runs alone); the bits are the same,
- * and LB_K_COLLIDE then counts a pair as one launch.  For
- * LB_BINARY on large lattices it is the single-pass march, which sums phi from
- * the pulled g and takes its stencils on chip; on small lattices (or with
- * LB_STEP_TWO_PASS) a phi kernel, then the fused collide (see
- * binary_step).  Paper: Section IV (collision) and Section II-A
+ * LB_SINGLE with vvl 0 or 1, lattices from 130000 (LB_F64), 200000 (LB_F32)
+ * or 2000000 (LB_F16, nx a multiple of 64 and ny of 8) sites take their steps
+ * two to a launch, the state between them staying on chip (an odd last step
+ * runs alone); the bits are the same, and LB_K_COLLIDE then counts a pair as
+ * one launch.  For LB_BINARY it is the single-pass march, which sums phi from
+ * the pulled g and takes its stencils on chip, or (small FP64 lattices,
+ * LB_STEP_TWO_PASS) a phi kernel, then the fused collide (see binary_step).  Paper: Section IV (collision) and Section II-A
  * (propagation, finite-difference gradients of phi). */
 int lb_step(lb_ctx* ctx, int32_t nsteps);
 
