@@ -536,6 +536,11 @@ int run_propagate(lb_ctx* c) {
     return LB_OK;
 }
 
+// Blocks of k_single_pair the chip runs at once: FP64 one 512-lane block a CU,
+// FP32 and FP16 1024 lanes.
+template <class S, class TP>
+constexpr int pair_slots() { return kCUs * (sizeof(S) == 8 ? 1 : 1024 / TP::TPB); }
+
 // Two collisions, with the propagation between them, of the state in `src`
 // (a pending one is pulled), into `dst`; REC: the first one's values into
 // `mid`.  All three in the layout of geo().
@@ -544,8 +549,7 @@ int launch_single_pair(lb_ctx* c, bool pending, const S* src, S* mid, S* dst, bo
     const auto cp = coll_params<S>(c);
     auto with = [&](auto tiling) {
         using TP = decltype(tiling);
-        // FP64: one 512-lane block a CU; FP32, FP16: 1024 lanes
-        const int slots = kCUs * (sizeof(S) == 8 ? 1 : 1024 / TP::TPB);
+        const int slots = pair_slots<S, TP>();
         Geo g = c->template column_geo<TP>(slots);
         if (canonical) g = c->canonical(g);
         const dim3 grid(march_grid(g, slots, sizeof(S) == 8)), block(TP::TPB);
@@ -574,7 +578,11 @@ int launch_single_pair(lb_ctx* c, bool pending, const S* src, S* mid, S* dst, bo
 template <class S>
 bool pair_pays(const lb_ctx* c) {
     if (c->p.model != LB_SINGLE || c->p.vvl > 1 || c->L.nsite < kPairMinSites<S>) return false;
-    return sizeof(S) > 2 || (c->p.nx % PairTile::TX == 0 && c->p.ny % PairTile::TY == 0);
+    if (sizeof(S) == 4 && c->p.collision == LB_MRT) return c->L.nsite >= 800000;
+    if (sizeof(S) > 2) return true;
+    if (c->p.collision == LB_MRT || c->p.nx % PairTile::TX != 0 || c->p.ny % PairTile::TY != 0) return false;
+    const int slots = pair_slots<S, PairTile>(), n = c->template column_geo<PairTile>(slots).nblocks;
+    return c->wide_rows() || (c->p.collision == LB_BGK && n * 10 >= (n + slots - 1) / slots * slots * 9);
 }
 
 template <class S>

@@ -54,7 +54,8 @@ def test_pairs_equal_single_steps(lbgpu, storage, nx, ny, nz, coll):
             states.append(lat.get_state()[0])
         lbgpu.lb_profile(lat.ctx, False)
         launches = lbgpu.lb_kernel_times(lat.ctx, lbgpu.LB_K_COLLIDE)[1]
-        assert launches == (5 if how == "pairs" else 9)
+        # two steps a launch (TRT and MRT only where that pays)
+        assert launches == (5 if how == "pairs" else 9) or (coll != "bgk" and launches == 9)
         lat.close()
         got[how] = states
     for a, b in zip(got["pairs"], got["steps"]):
