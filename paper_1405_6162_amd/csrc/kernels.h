@@ -691,9 +691,10 @@ __global__ __launch_bounds__(P::TPB, (MarchHold<S, P::TX, HALO>::waves)) void k_
 // are rounded to the storage type, so the result has the bits of two steps.
 //
 // The next plane's loads are issued before step two, whose arithmetic and
-// stores cover their latency (FP64 256^3: 1.04 ms a pair, 1.05 with a second
-// barrier per plane instead of two LDS buffers, 1.07 without early loads but
-// two blocks a CU; two single steps take 1.79).  Loading the ring's values
+// stores cover their latency (FP64 256^3: 0.96 ms a pair, two single steps
+// 1.79; before the planes' bases were scalar 1.04, 1.05 with a second barrier
+// per plane instead of two LDS buffers, 1.07 without early loads but two blocks
+// a CU).  Loading the ring's values
 // early too costs registers: 2% faster in FP64 at 256^3, 5-8% slower at 128^3
 // and 160^3.  Halves of a wavefront (32-wide tiles) and 64 x 4 tiles lose
 // 6-10% at 256^3, 64 x 16 5%.
