@@ -191,8 +191,11 @@ int lb_propagate(lb_ctx* ctx);
  * whose 64-wide tiles also want LB_BGK and a chip nine tenths full); the bits are the same, and LB_K_COLLIDE then counts a pair as
  * one launch.  For LB_BINARY it is the single-pass march, which sums phi from
  * the pulled g and takes its stencils on chip, or (small FP64 lattices,
- * LB_STEP_TWO_PASS) a phi kernel, then the fused collide (see binary_step).  Paper: Section IV (collision) and Section II-A
- * (propagation, finite-difference gradients of phi). */
+ * LB_STEP_TWO_PASS) a phi kernel, then the fused collide (see binary_step).
+ * Captured into a graph on a pending state, an even number of steps leaves
+ * the state in the buffer it was in, so replaying the graph advances it.
+ * Paper: Section IV (collision) and Section II-A (propagation,
+ * finite-difference gradients of phi). */
 int lb_step(lb_ctx* ctx, int32_t nsteps);
 
 /* Moments of the current state, FP64: rho[N], u[3*N] component-major, and

@@ -585,18 +585,32 @@ bool pair_pays(const lb_ctx* c) {
     return c->wide_rows() || (c->p.collision == LB_BGK && n * 10 >= (n + slots - 1) / slots * slots * 9);
 }
 
+// Whether the context's stream is being captured into a graph (the null
+// stream never is).
+inline bool capturing(const lb_ctx* c) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (c->stream && hipStreamIsCapturing(c->stream, &status) != hipSuccess) (void)hipGetLastError();
+    return status != hipStreamCaptureStatusNone;
+}
+
+// A step taken alone moves the state to the other buffer, but for the first
+// from a direct state; so does a pair.  A captured call has to leave the state
+// in the buffer where its steps taken alone would, since a graph is replayed on
+// fixed buffers: an even number of steps from a pending state ends where it
+// began and advances the state at every replay.  There, pairs are taken in an
+// even number (from a direct state in an odd one) and the other steps alone.
 template <class S>
 int run_step(lb_ctx* c, int32_t n) {
-    if (pair_pays<S>(c)) {
-        for (; n >= 2; n -= 2) {
-            const S* src = (const S*)c->fbuf(c->cur);
-            S* dst = (S*)c->fbuf(1 - c->cur);
-            const int rc = c->L.blocked ? launch_single_pair<S, true, false>(c, c->pending, src, nullptr, dst, false)
-                                        : launch_single_pair<S, false, false>(c, c->pending, src, nullptr, dst, false);
-            if (rc) return rc;
-            c->cur = 1 - c->cur;
-            c->pending = true;
-        }
+    int32_t pairs = pair_pays<S>(c) ? n / 2 : 0;
+    if (pairs > 0 && (pairs & 1) == (c->pending ? 1 : 0) && capturing(c)) --pairs;
+    for (; pairs > 0; --pairs, n -= 2) {
+        const S* src = (const S*)c->fbuf(c->cur);
+        S* dst = (S*)c->fbuf(1 - c->cur);
+        const int rc = c->L.blocked ? launch_single_pair<S, true, false>(c, c->pending, src, nullptr, dst, false)
+                                    : launch_single_pair<S, false, false>(c, c->pending, src, nullptr, dst, false);
+        if (rc) return rc;
+        c->cur = 1 - c->cur;
+        c->pending = true;
     }
     for (int32_t k = 0; k < n; ++k) {
         int rc = run_collide<S>(c);
