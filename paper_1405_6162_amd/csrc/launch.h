@@ -735,7 +735,9 @@ int run_set_state(lb_ctx* c, const S* f, const S* g) {
 
 // nsteps binary steps whose post-collision fields go to canonical memory, f
 // then g of step k to post + k*38*N; afterwards the state is pending on a copy
-// of the last of them.  Step 0 collides the context's state into post[0] (128^3:
+// of the last of them, in the other buffer where it was pending before: the
+// buffer the record started from stays as it is, so a graph of the call records
+// the same steps at every replay.  Step 0 collides the context's state into post[0] (128^3:
 // 360 us with its phi; in the context's buffers and copied out it was 600);
 // later steps march from post[k-1] to post[k] (both of direction stride N).
 template <class S>
@@ -803,9 +805,11 @@ int run_step_record_binary(lb_ctx* c, int32_t n, S* post, typename Compute<S>::T
     {
         Timed t(c, LB_K_OTHER);
         const S* last = post + (size_t)(n - 1) * 2 * Q * N;
-        rc = run_convert<S>(c, last, last + Q * N, (S*)c->fbuf(c->cur), (S*)c->gbuf(c->cur), c->canonical_geo(),
+        const int dst = c->pending ? 1 - c->cur : c->cur;
+        rc = run_convert<S>(c, last, last + Q * N, (S*)c->fbuf(dst), (S*)c->gbuf(dst), c->canonical_geo(),
                             c->geo());
         if (rc) return rc;
+        c->cur = dst;
     }
     c->pending = true;
     return LB_OK;
