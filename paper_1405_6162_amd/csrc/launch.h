@@ -185,6 +185,37 @@ inline Layout layout_of(const lb_params* p) {
     return L;
 }
 
+// Chunks a marching kernel cuts nz planes into, `columns` tile columns and
+// `slots` blocks at a time.  A chunk of d planes costs about d + 3 (its ends take
+// two planes of phi, or of step one, more): nz is cut, evenly, into the number
+// of chunks (at most 128 planes each) that makes rounds x (d + 3) least.
+// Measured against fixed depths: pair, 256^3 FP64, 926 us with 2 chunks (one
+// round), 1045 with 4; 128^3 128 with 8 (one round), 145 with 16.  March, FP64:
+// 96^3 115 us with 10 chunks (240 blocks), 148 with 6; 160^3 496 with 4 (one
+// round), 520 with 8; 64^3 31 with 32 chunks of 2 planes against 92 with 4 of 16
+// (the two-pass step: 40).
+//
+// This runs at every launch, so it may not take time that grows with nz (1 x 1 x
+// 4e8, every count tried: 0.9 s a launch).  All counts from c to the last that
+// needs no more rounds cost the least at their least depth, whose fewest
+// chunks are taken; and no count from c on costs less than columns x nz / slots
+// + 3 rounds(c), where the search ends: 10 to 100 counts.
+inline int chunks_of(int64_t columns, int nz, int slots) {
+    int64_t best = INT64_MAX;
+    int chunks = 1;
+    for (int64_t c = lbk::tiles(nz, 128); c <= nz;) {
+        const int64_t rounds = (columns * c + slots - 1) / slots;
+        if (columns * nz / slots + 3 * rounds >= best) break;
+        const int64_t last = std::min<int64_t>(nz, rounds * slots / columns), depth = (nz + last - 1) / last;
+        if (rounds * (depth + 3) < best) {
+            best = rounds * (depth + 3);
+            chunks = (int)std::max(c, (nz + depth - 1) / depth);
+        }
+        c = last + 1;
+    }
+    return chunks;
+}
+
 struct Rec { int kind; hipEvent_t start, stop; };
 
 }  // namespace lbl
@@ -229,27 +260,14 @@ struct lb_ctx {
         g.nblocks = g.gx * g.gy * g.gz;
         return g;
     }
-    // Tiling of a marching kernel (k_binary_march, k_single_pair).  A chunk of
-    // d planes costs about d + 3 (its ends take two planes of phi, or of step
-    // one, more) and the chip runs `slots` blocks at a time: nz is cut, evenly,
-    // into the number of chunks (at most 128 planes each) that makes
-    // rounds x (d + 3) least.  Measured against fixed depths: pair, 256^3 FP64,
-    // 926 us with 2 chunks (one round), 1045 with 4; 128^3 128 with 8 (one
-    // round), 145 with 16.  March, FP64: 96^3 115 us with 10 chunks (240
-    // blocks), 148 with 6; 160^3 496 with 4 (one round), 520 with 8; 64^3 31
-    // with 32 chunks of 2 planes against 92 with 4 of 16 (the two-pass step: 40).
+    // Tiling of a marching kernel (k_binary_march, k_single_pair) of which the
+    // chip runs `slots` blocks at a time.
     template <class TP>
     lbk::Geo column_geo(int slots) const {
         lbk::Geo g = geo();
         g.gx = lbk::tiles(p.nx, TP::TX);
         g.gy = lbk::tiles(p.ny, TP::TY);
-        const int64_t col = (int64_t)g.gx * g.gy;
-        int64_t best = INT64_MAX;
-        g.gz = 1;
-        for (int c = lbk::tiles(p.nz, 128); c <= p.nz; ++c) {
-            const int64_t cost = (col * c + slots - 1) / slots * (lbk::tiles(p.nz, c) + 3);
-            if (cost < best) { best = cost; g.gz = c; }
-        }
+        g.gz = lbl::chunks_of((int64_t)g.gx * g.gy, p.nz, slots);
         g.nblocks = g.gx * g.gy * g.gz;
         return g;
     }
