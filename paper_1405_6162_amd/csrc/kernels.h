@@ -939,14 +939,18 @@ __global__ __launch_bounds__(P::TPB) void k_moments(const S* __restrict__ f, con
 }
 
 // ---------------------------------------------------------------------------
-// Deterministic reductions: per-block tree in LDS, then one block summing the
-// block partials in index order.
+// Deterministic reductions: every lane takes its sites in order, a block's lanes
+// are combined by a tree in LDS, and one block combines the blocks' values, lane
+// t those of blocks t, t + TPB, ... and then by the same tree.
 // ---------------------------------------------------------------------------
 
-// Tree sum over the block of K values per thread, in a fixed order; on return
-// sh[k][0] holds the block total of value k (visible to every thread).
-template <int TPB, int K>
-__device__ __forceinline__ void block_tree_sum(const double (&v)[K], double (*sh)[TPB]) {
+// Tree over the block of K values per thread, combined by op(k, a, b), in a
+// fixed order; on return sh[k][0] holds the block's value k (visible to every
+// thread).  All K values go through the tree together: wavefronts that each
+// shuffled a share of the values took longer, which shows on small lattices
+// (lb_field_stats with 10 values, FP64 16^3 to 64^3: 2.8-3.4 us a call).
+template <int TPB, int K, class OP>
+__device__ __forceinline__ void block_tree(const double (&v)[K], double (*sh)[TPB], OP&& op) {
     const int t = threadIdx.x;
 #pragma unroll
     for (int k = 0; k < K; ++k) sh[k][t] = v[k];
@@ -954,32 +958,15 @@ __device__ __forceinline__ void block_tree_sum(const double (&v)[K], double (*sh
     for (int half = TPB / 2; half > 0; half >>= 1) {
         if (t < half) {
 #pragma unroll
-            for (int k = 0; k < K; ++k) sh[k][t] = sh[k][t] + sh[k][t + half];
+            for (int k = 0; k < K; ++k) sh[k][t] = op(k, sh[k][t], sh[k][t + half]);
         }
         __syncthreads();
     }
 }
 
-// Sum (or minimum, maximum: `op`) over the block of K values per thread, in a
-// fixed order; thread 64 w of wavefront w hands total k of those with
-// k mod (TPB / 64) == w to put(k, total).  The wavefronts share the values out,
-// so each only shuffles K / 4 of them.
-template <int TPB, int K, class OP, class F>
-__device__ __forceinline__ void block_reduce(const double (&v)[K], OP&& op, F&& put) {
-    constexpr int W = TPB / 64;
-    __shared__ double sh[K][TPB];
-    const int t = threadIdx.x, lane = t & 63;
-#pragma unroll
-    for (int k = 0; k < K; ++k) sh[k][t] = v[k];
-    __syncthreads();
-    for (int k = t >> 6; k < K; k += W) {
-        double r = sh[k][lane];
-#pragma unroll
-        for (int w = 1; w < W; ++w) r = op(k, r, sh[k][lane + 64 * w]);
-#pragma unroll
-        for (int d = 32; d > 0; d >>= 1) r = op(k, r, __shfl_down(r, d, 64));
-        if (lane == 0) put(k, r);
-    }
+template <int TPB, int K>
+__device__ __forceinline__ void block_tree_sum(const double (&v)[K], double (*sh)[TPB]) {
+    block_tree<TPB, K>(v, sh, [](int, double a, double b) { return a + b; });
 }
 
 // Calls fn(site) for the sites of this block's share of the lattice's tiles:
@@ -1027,8 +1014,9 @@ __global__ __launch_bounds__(P::TPB) void k_sums_partial(const S* __restrict__ f
             if constexpr (MODEL == MODEL_BINARY) v5[4] = v5[4] + static_cast<double>(gv[i]);
         });
     });
-    block_reduce<P::TPB>(v5, [](int, double a, double b) { return a + b; },
-                         [&](int k, double r) { partial[8 * (size_t)blockIdx.x + k] = r; });
+    __shared__ double sh[5][P::TPB];
+    block_tree_sum<P::TPB, 5>(v5, sh);
+    if (threadIdx.x < 5) partial[8 * (size_t)blockIdx.x + threadIdx.x] = sh[threadIdx.x][0];
 }
 
 // out[k] = base[k] + sum_b partial[8 b + k], k < K; one block of P::TPB threads.
@@ -1064,8 +1052,7 @@ __global__ __launch_bounds__(P::TPB) void k_sums_final(const double* __restrict_
 // ---------------------------------------------------------------------------
 // Field statistics of the current state (device reductions, fixed order):
 // 0 sum rho, 1-3 sum j, 4 sum phi, 5 sum rho u.u, 6 min phi, 7 max phi,
-// 8 sum phi^2, 9 max u.u.  Sums per block by an LDS tree, then one block over
-// the block partials in index order; min and max likewise.
+// 8 sum phi^2, 9 max u.u.  Each by the same tree.
 // ---------------------------------------------------------------------------
 
 constexpr int NSTAT = 10;
@@ -1108,7 +1095,9 @@ __global__ __launch_bounds__(P::TPB) void k_stats_partial(const S* __restrict__ 
             v[8] += phi * phi;
         }
     });
-    block_reduce<P::TPB>(v, combine_stat, [&](int k, double r) { partial[16 * (size_t)blockIdx.x + k] = r; });
+    __shared__ double sh[NSTAT][P::TPB];
+    block_tree<P::TPB, NSTAT>(v, sh, combine_stat);
+    if (threadIdx.x < NSTAT) partial[16 * (size_t)blockIdx.x + threadIdx.x] = sh[threadIdx.x][0];
 }
 
 template <class P>
@@ -1121,10 +1110,12 @@ __global__ __launch_bounds__(P::TPB) void k_stats_final(const double* __restrict
 #pragma unroll
         for (int k = 0; k < NSTAT; ++k) v[k] = combine_stat(k, v[k], q[k]);
     }
-    block_reduce<P::TPB>(v, combine_stat, [&](int k, double r) {
-        const bool of_phi = k == 4 || (k >= 6 && k <= 8);
-        out[k] = of_phi && !binary ? 0.0 : r;
-    });
+    __shared__ double sh[NSTAT][P::TPB];
+    block_tree<P::TPB, NSTAT>(v, sh, combine_stat);
+    if (t < NSTAT) {
+        const bool of_phi = t == 4 || (t >= 6 && t <= 8);
+        out[t] = of_phi && !binary ? 0.0 : sh[t][0];
+    }
 }
 
 // ---------------------------------------------------------------------------
