@@ -278,17 +278,24 @@ __device__ __forceinline__ void collide_single(const T (&f)[Q], const CollParams
     if constexpr (COLL != COLL_BGK) relax_parts<COLL, S>(f, neq, cp, put);
 }
 
-// collide_single, stored: every post-collision value before the first store
-// (measured 1.3% faster than storing each as it is computed).
+// collide_single, stored.  BGK: every post-collision value before the first store
+// (measured 1.3% faster than storing each as it is computed).  TRT and MRT, whose
+// values come last and one by one: each as it is computed (us a step, so / all
+// before the first store: FP16 TRT 192 x 232 x 134 82.6 / 88.7, FP16 MRT 256^3
+// 258 / 264, FP32 TRT 192 x 232 x 134 152.0 / 155.6, FP64 305 / 314).
 template <class P, int COLL = COLL_BGK, class S, class T>
 __device__ __forceinline__ void relax_single(const T (&f)[Q], S* fdst, uint32_t off, const Geo& geo,
                                              const CollParams<T>& cp) {
-    S out[Q];
-    collide_single<COLL, S>(f, cp, [&](auto I, S v) { out[decltype(I)::value] = v; });
-    static_for<0, Q>([&](auto I) {
-        constexpr int i = decltype(I)::value;
-        stg<P::nt_store, S, wide_of<P, S>>(fdst + i * geo.dstride, off, out[i]);
-    });
+    auto store = [&](auto I, S v) {
+        stg<P::nt_store, S, wide_of<P, S>>(fdst + decltype(I)::value * geo.dstride, off, v);
+    };
+    if constexpr (COLL != COLL_BGK) {
+        collide_single<COLL, S>(f, cp, store);
+    } else {
+        S out[Q];
+        collide_single<COLL, S>(f, cp, [&](auto I, S v) { out[decltype(I)::value] = v; });
+        static_for<0, Q>([&](auto I) { store(I, out[decltype(I)::value]); });
+    }
 }
 
 // Central differences and the 7-point Laplacian of phi, from the six
