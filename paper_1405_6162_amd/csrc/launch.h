@@ -30,13 +30,19 @@ using Pol = Tiling<64, 4, 1, false, true, true>;
 // The same with ordinary stores: for states that stay in the 256 MB memory-side
 // cache (kCachedBytes, both copies of every distribution), from which the next
 // step then reads them.  us a step, ordinary / nontemporal stores: binary FP16
-// 96^3 34 / 47, 112^3 (213 MB) 44 / 65, FP32 48^3 11.3 / 14.8, FP64 64^3 31 / 35;
-// single fluid in pairs FP32 96^3 15.6 / 19.7, 112^3 22.9 / 30.0; beyond the
-// cache they lose: FP64 128^3 261 / 247, 256^3 1919 / 1819.
+// 96^3 34 / 47, 112^3 (213 MB) 44 / 65, FP32 48^3 11.2 / 14.9, FP64 64^3 31 / 34;
+// single fluid in pairs FP32 96^3 15.6 / 19.7, 112^3 22.9 / 30.0, one at a time
+// FP64 64^3 12.9 / 17.0; beyond the cache they lose: FP64 128^3 261 / 247, 256^3
+// 1919 / 1819.  So they do where a single fluid's state fits the eight 4 MB L2
+// caches (kL2Bytes; BGK and TRT three quarters of them), which have to write
+// back what they hold after every launch: FP16 BGK 64^3 (20 MB) 5.4 / 5.2, 320 x 320
+// x 2 (16 MB) 5.8 / 4.9, MRT 60^3 7.5 / 6.3, FP32 56^3 (30 MB) MRT 6.9 / 6.2, BGK
+// 6.1 / 6.9; 64^3 (40 MB) MRT 8.2 / 9.3.  The march gains at all sizes.
 template <class P> using Cached = Tiling<P::TX, P::TY, P::TZ, P::nt_load, false, P::xcd>;
 // The same for blocked states of 4 GiB and more a buffer (layout_of).
 template <class P> using Wide = Tiling<P::TX, P::TY, P::TZ, P::nt_load, P::nt_store, P::xcd, true>;
 constexpr size_t kCachedBytes = 280000000;
+constexpr size_t kL2Bytes = 32000000;
 // Pol with 2 and 4 sites per lane along z (lb_params.vvl).
 using Pol2 = Tiling<64, 4, 2, false, true, true>;
 using Pol4 = Tiling<64, 4, 4, false, true, true>;
@@ -271,8 +277,18 @@ struct lb_ctx {
         g.nblocks = g.gx * g.gy * g.gz;
         return g;
     }
-    // Whether the state stays in the memory-side cache (see Cached).
-    bool cached() const { return L.dist_bytes * (p.model == LB_BINARY ? 4 : 2) <= lbl::kCachedBytes; }
+    // Whether ordinary stores keep the state where the next step reads it (see Cached).
+    bool cached() const {
+        if (p.model == LB_BINARY) return 4 * L.dist_bytes <= lbl::kCachedBytes;
+        const size_t least = p.collision == LB_MRT ? lbl::kL2Bytes : lbl::kL2Bytes / 4 * 3;
+        return 2 * L.dist_bytes > least && 2 * L.dist_bytes <= lbl::kCachedBytes;
+    }
+    // The same for copies between the state and the caller's arrays, of which one
+    // side is not read again: only where rows end within 64 bytes, which a
+    // nontemporal store then writes in parts.  us a copy out, ordinary /
+    // nontemporal: FP32 100^3 28.7 / 37.1, binary FP16 80^3 17.5 / 25.4; rows of
+    // whole 64 bytes FP32 64^3 6.1 / 5.2, 80^3 15.0 / 14.3, binary FP64 48^3 12.4 / 10.7.
+    bool cached_copy() const { return cached() && (size_t)p.nx * lbl::storage_size(p.storage) % 64 != 0; }
     // Whether 128-wide tiles leave no more lanes of a row idle than 64-wide ones.
     bool wide_rows() const { return lbk::tiles(p.nx, 128) * 2 == lbk::tiles(p.nx, 64); }
     dim3 grid() const { return dim3(L.nblocks); }
@@ -517,10 +533,10 @@ int run_collide(lb_ctx* c) {
 }
 
 // Copy a state (f, and g for the binary model) from layout sgeo to layout
-// dgeo, site by site (the context's layout <-> canonical caller memory), pulled
-// when GATHER.
+// dgeo, site by site (the context's layout <-> canonical caller memory, or its
+// own layout to itself), pulled when GATHER; with ordinary stores if `cached`.
 template <class S, bool GATHER>
-int run_copy(lb_ctx* c, const S* fs, const S* gs, S* fd, S* gd, const Geo& sgeo, const Geo& dgeo) {
+int run_copy(lb_ctx* c, const S* fs, const S* gs, S* fd, S* gd, const Geo& sgeo, const Geo& dgeo, bool cached) {
     auto with = [&](auto pol) {
         using P = decltype(pol);
         if (c->p.model == LB_BINARY)
@@ -529,26 +545,26 @@ int run_copy(lb_ctx* c, const S* fs, const S* gs, S* fd, S* gd, const Geo& sgeo,
             k_stream<P, S, GATHER><<<c->grid(), c->block(), 0, c->stream>>>(fs, fd, sgeo, dgeo);
         return launch_status();
     };
-    return c->L.wide ? with(Wide<Pol>{}) : (c->cached() ? with(Cached<Pol>{}) : with(Pol{}));
+    return c->L.wide ? with(Wide<Pol>{}) : (cached ? with(Cached<Pol>{}) : with(Pol{}));
 }
 
 // Materialise propagate(buffer[src]) into (f, g) of layout dgeo.
 template <class S>
-int run_stream_into(lb_ctx* c, int src, S* f, S* g, const Geo& dgeo) {
+int run_stream_into(lb_ctx* c, int src, S* f, S* g, const Geo& dgeo, bool cached) {
     Timed t(c, LB_K_STREAM);
-    return run_copy<S, true>(c, (const S*)c->fbuf(src), (const S*)c->gbuf(src), f, g, c->geo(), dgeo);
+    return run_copy<S, true>(c, (const S*)c->fbuf(src), (const S*)c->gbuf(src), f, g, c->geo(), dgeo, cached);
 }
 
 template <class S>
 int run_convert(lb_ctx* c, const S* fs, const S* gs, S* fd, S* gd, const Geo& sgeo, const Geo& dgeo) {
-    return run_copy<S, false>(c, fs, gs, fd, gd, sgeo, dgeo);
+    return run_copy<S, false>(c, fs, gs, fd, gd, sgeo, dgeo, c->cached_copy());
 }
 
 template <class S>
 int run_propagate(lb_ctx* c) {
     if (!c->pending) { c->pending = true; return LB_OK; }   // propagation of a direct buffer is deferred
     const int dst = 1 - c->cur;
-    int rc = run_stream_into<S>(c, c->cur, (S*)c->fbuf(dst), (S*)c->gbuf(dst), c->geo());
+    int rc = run_stream_into<S>(c, c->cur, (S*)c->fbuf(dst), (S*)c->gbuf(dst), c->geo(), c->cached());
     if (rc) return rc;
     c->cur = dst;
     return LB_OK;
@@ -736,7 +752,7 @@ int run_stats(lb_ctx* c, double* out) {
 
 template <class S>
 int run_get_state(lb_ctx* c, S* f, S* g) {
-    if (c->pending) return run_stream_into<S>(c, c->cur, f, g, c->canonical_geo());
+    if (c->pending) return run_stream_into<S>(c, c->cur, f, g, c->canonical_geo(), c->cached_copy());
     Timed t(c, LB_K_OTHER);
     return run_convert<S>(c, (const S*)c->fbuf(c->cur), (const S*)c->gbuf(c->cur), f, g, c->geo(),
                           c->canonical_geo());
