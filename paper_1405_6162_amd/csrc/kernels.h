@@ -433,7 +433,7 @@ __global__ __launch_bounds__(P::TPB) void k_collide_single_strided(const S* fsrc
 // geo.gz chunks of z planes.  phi(s) = phi0 + sum_i e_i(s - c_i) needs the pulled
 // g of s, which the collision of s needs anyway: each lane gathers g for
 // plane z+1, sums it into the plane's phi tile in LDS and keeps the 19 values
-// for the next plane's collision, in registers or (GLDS) in LDS.
+// for the next plane's collision, in registers or in LDS.
 // The x/y halo ring of the
 // tile (2 TX + 2 TY sites per plane) is summed by one lane each from its own
 // gather; the chunk's first and last plane need one extra plane of phi each.
@@ -542,14 +542,10 @@ __device__ __forceinline__ T phi_stored(const S (&e)[Q], T phi0) {
     return phi_sum<typename Accum<S>::T>(v, phi0);
 }
 
-// How the march holds its values, per storage type and tile.
-//   early:      the next plane's f and g are loaded before this plane's
-//               collision, whose arithmetic and stores cover their latency (a
-//               load issued after the stores would also wait for them).  In
-//               FP16 only with 64 x 8 tiles: 160^3 173 against 183 us, 192^3
-//               237 against 253; with 128 x 4 ones, whose ring is another 264
-//               gathers, it costs 1% at 384^3.
-//   early_halo: the ring's g too (FP32, template flag HALO).
+// How the march holds its values, per storage type and AHEAD, what is loaded
+// before this plane's collision, whose arithmetic and stores cover the latency
+// (a load issued after the stores would also wait for them): 0 nothing, 1 the
+// next plane's f and g, 2 the ring's g too (launch_march says which).
 //   in_lds:     the next plane's g waits in LDS (each lane only touches its own
 //               slots, so no barrier is involved) instead of in registers:
 //               in FP64 a plane's f and g and the next one's are 304 VGPRs.
@@ -560,21 +556,21 @@ __device__ __forceinline__ T phi_stored(const S (&e)[Q], T phi0) {
 //   waves:      per SIMD, which sets how many 512-lane blocks a CU holds.
 // FP64 256^3: 1816 us a step early, 1850 not; FP32 256^3 897, 986 not early
 // at four waves; FP16 256^3 543.
-template <class S, int TX, bool HALO>
+template <class S, int AHEAD>
 struct MarchHold {
-    static constexpr bool early = sizeof(S) > 2 || TX == 64, early_halo = early && HALO, in_lds = sizeof(S) != 4;
+    static constexpr bool early = AHEAD > 0, early_halo = AHEAD == 2, in_lds = sizeof(S) != 4;
     static constexpr int planes = 4, waves = sizeof(S) == 2 ? 4 : 2;
 };
 
 // With PHI_OUT the kernel also stores the phi it computes for its own sites
 // (phi_out[s], canonical), i.e. phi of the state this step collides.
 // BLK: the arrays are in the blocked layout.
-template <class P, class S, bool PHI_OUT, int COLL, bool BLK, bool HALO>
-__global__ __launch_bounds__(P::TPB, (MarchHold<S, P::TX, HALO>::waves)) void k_binary_march(
+template <class P, class S, bool PHI_OUT, int COLL, bool BLK, int AHEAD>
+__global__ __launch_bounds__(P::TPB, (MarchHold<S, AHEAD>::waves)) void k_binary_march(
     const S* __restrict__ fsrc, const S* __restrict__ gsrc, S* __restrict__ fdst, S* __restrict__ gdst, Geo geo,
     CollParams<typename Compute<S>::T> cp, typename Compute<S>::T* __restrict__ phi_out) {
     using T = typename Compute<S>::T;
-    using H = MarchHold<S, P::TX, HALO>;
+    using H = MarchHold<S, AHEAD>;
     constexpr int TX = P::TX, TY = P::TY, LX = TX + 2, RING = H::planes;
     static_assert(2 * TX + 2 * TY <= P::TPB, "one halo site per lane");
     __shared__ T ring[RING][(TY + 2) * LX];

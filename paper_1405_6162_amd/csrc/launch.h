@@ -57,16 +57,12 @@ constexpr int kCUs = 256;
 // a cache line of their own, 2 or 4 bytes used), is used where its rows leave
 // no more lanes idle than 64-site rows (nx mod 128 is 0 or above 64): 200 x 204
 // x 100 289 against 297 us in FP32, 384^3 1817 against 1840 in FP16.
-// FP32 loads the ring's g early too with those tiles and, with 64 x 8 ones, from
-// kEarlyHaloSites up: 192^3 419 against 432 us, 320^3 1947 against 1996; 160^3
-// 261 against 250.
 using MarchTile = Tiling<64, 8, 1, false, true, true>;
 using MarchTileWide = Tiling<128, 4, 1, false, true, true>;
 // Blocks of the march the chip runs at once: one 512-lane block a CU where it
 // is compiled for two waves per SIMD (FP64, FP32), two for four (FP16).
 template <class S>
-constexpr int march_slots() { return kCUs * MarchHold<S, 64, false>::waves * 4 * 64 / MarchTile::TPB; }
-constexpr int64_t kEarlyHaloSites = 6000000;
+constexpr int march_slots() { return kCUs * MarchHold<S, 0>::waves * 4 * 64 / MarchTile::TPB; }
 // Two single-fluid steps per launch (k_single_pair).  A CU holds one 512-lane
 // block in FP64 (128 KB of LDS, up to 256 VGPRs a lane), and 1024 lanes in
 // FP32 and FP16 (128 VGPRs): two blocks of 64 x 8 or, where 128-wide rows
@@ -412,43 +408,83 @@ void by_collision(const lb_ctx* c, F&& fn) {
 // the lattice; in launch order the chip sweeps one place, whose neighbour lines
 // then come from the memory-side cache.  us a step, launch / XCD order: several
 // rounds, FP64 320^3 binary 3652 / 3808, single 1001 / 1044, 300 x 240 x 220
-// binary 1927 / 2022, FP32 320^3 binary 1881 / 1960; one round, FP64 256^3
-// binary 1864 / 1820, single 505 / 479, 128^3 256 / 245, FP32 256^3 932 / 907.
-// FP32 pairs and FP16 show no rule (-5 to +3%) and keep XCD order.
-inline unsigned march_grid(const Geo& g, int slots, bool by_rounds) {
+// binary 1927 / 2022, FP32 320^3 binary 1881 / 1960, 512 x 512 x 24 367 / 388; one
+// round, FP64 256^3 binary 1864 / 1820, single 505 / 479, 128^3 256 / 245, FP32
+// 256^3 932 / 907.  FP32 pairs and FP16 show no rule (-5 to +3%) and keep XCD order.
+// So do the march's chunks of 3 to 15 planes: they are no sweep worth the name,
+// and what their ends read again comes from an XCD's own L2 (march_order).
+inline unsigned march_grid(const Geo& g, int slots, bool launch_order) {
     const int n = g.nblocks;
-    if (by_rounds && n > slots) return (unsigned)(n % 8 != 0 ? n : n + 1);
+    if (launch_order && n > slots) return (unsigned)(n % 8 != 0 ? n : n + 1);
     return (unsigned)((n + 7) / 8 * 8);
+}
+
+// Whether the march's tiles go in launch order where they need several rounds.
+// us a step, launch / XCD order: FP32 512 x 512 x 4 79.7 / 70.3, x 12 193.4 / 189.0,
+// 1024 x 1024 x 4 272 / 260, FP64 512 x 512 x 4 138 / 133; one and two planes go
+// either way (FP32 2048 x 2048 x 2 500 / 522, FP64 1061 / 1041), and so do pairs at
+// every depth (FP64 512 x 512 x 4 40.8 / 42.2, x 2 24.7 / 21.2).
+template <class S>
+bool march_order(const Geo& g) {
+    const int depth = tiles(g.nz, g.gz);
+    return sizeof(S) > 2 && (depth < 3 || depth > 15);
 }
 
 // One march from the pending state (fs, gs) to (fd, gd), all in the layout of
 // geo() or canonical; phi, if not NULL, receives the order parameter of the
 // state it collides.
+//
+// What is loaded ahead (MarchHold): the next plane's f and g, in FP16 only with
+// 64 x 8 tiles (160^3 173 against 183 us, 192^3 237 against 253; with 128 x 4 ones,
+// whose ring is another 264 gathers, it costs 1% at 384^3); in FP32 the ring's g
+// too with 128 x 4 tiles and, with 64 x 8 ones, from 6 million sites up (192^3 419
+// against 432 us, 320^3 1947 against 1996; 160^3 261 against 250).  Not in FP64 and
+// FP32 chunks of 4 to 7 planes beyond the cache, taken in several rounds, where
+// filling the pipeline is much of a block's work: FP32 512 x 512 x 4 66.8 against
+// 70.3, 1024 x 1024 x 4 256 against 260, FP64 512 x 512 x 4 131.7 against 133.0, x 6
+// 195 against 197; x 8 equal, 1024 x 1024 x 8 FP32 512 against 495.
 template <class S, bool BLK, bool PHI_OUT>
 int launch_march(lb_ctx* c, const S* fs, const S* gs, S* fd, S* gd, bool canonical, typename Compute<S>::T* phi) {
     const auto cp = coll_params<S>(c);
-    auto with = [&](auto tiling, auto halo) {
+    auto with = [&](auto tiling, auto ahead) {
         using TP = decltype(tiling);
         Geo g = c->template column_geo<TP>(march_slots<S>());
         if (canonical) g = c->canonical(g);
         Timed t(c, LB_K_COLLIDE);
         by_collision(c, [&](auto coll) {
-            k_binary_march<TP, S, PHI_OUT, decltype(coll)::value, BLK, decltype(halo)::value>
-                <<<march_grid(g, march_slots<S>(), sizeof(S) > 2), TP::TPB, 0, c->stream>>>(fs, gs, fd, gd, g, cp, phi);
+            k_binary_march<TP, S, PHI_OUT, decltype(coll)::value, BLK, decltype(ahead)::value>
+                <<<march_grid(g, march_slots<S>(), march_order<S>(g)), TP::TPB, 0, c->stream>>>(fs, gs, fd, gd, g, cp, phi);
         });
     };
     // records and structure-of-arrays states are far larger than the cache
-    auto launch = [&](auto tiling, auto halo) {
+    auto launch = [&](auto tiling, auto ahead) {
+        using TP = decltype(tiling);
         if constexpr (BLK && !PHI_OUT) {
-            if (c->cached()) { with(Cached<decltype(tiling)>{}, halo); return; }
+            if (c->cached()) { with(Cached<TP>{}, ahead); return; }
+            if constexpr (sizeof(S) > 2) {
+                const Geo g = c->template column_geo<TP>(march_slots<S>());
+                const int depth = tiles(g.nz, g.gz);
+                if (g.nblocks > march_slots<S>() && depth >= 4 && depth < 8) {
+                    with(tiling, std::integral_constant<int, 0>{});
+                    return;
+                }
+            }
         }
-        with(tiling, halo);
+        with(tiling, ahead);
     };
-    constexpr std::integral_constant<bool, sizeof(S) == 4> fp32{};
-    if constexpr (sizeof(S) == 8) launch(MarchTile{}, std::false_type{});
-    else if (c->wide_rows()) launch(MarchTileWide{}, fp32);
-    else if (fp32 && c->L.nsite >= kEarlyHaloSites) launch(MarchTile{}, fp32);
-    else launch(MarchTile{}, std::false_type{});
+    constexpr std::integral_constant<int, 0> nothing{};
+    constexpr std::integral_constant<int, 1> own{};
+    constexpr std::integral_constant<int, 2> ring{};
+    if constexpr (sizeof(S) == 8) {
+        launch(MarchTile{}, own);
+    } else if constexpr (sizeof(S) == 4) {
+        if (c->wide_rows()) launch(MarchTileWide{}, ring);
+        else if (c->L.nsite >= 6000000) launch(MarchTile{}, ring);
+        else launch(MarchTile{}, own);
+    } else {
+        if (c->wide_rows()) launch(MarchTileWide{}, nothing);
+        else launch(MarchTile{}, own);
+    }
     return launch_status();
 }
 
