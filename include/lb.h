@@ -94,9 +94,11 @@ extern "C" {
  * stencils on chip (608 B/site in FP64): fastest on large lattices.
  * LB_STEP_TWO_PASS: a phi pass, then the fused collide (776 B/site), every
  * site in parallel: fastest on small FP64 lattices, where the few blocks of
- * the march each run their planes in sequence.  LB_STEP_AUTO (0, the
- * default): with vvl 0 or 1 the march in LB_F32 and LB_F16 and, in LB_F64,
- * from 200000 sites; with more sites per lane the march from 128^3 sites;
+ * the march each run their planes in sequence, and on lattices of few rows,
+ * which leave much of a block idle.  LB_STEP_AUTO (0, the default): with vvl
+ * 0 or 1 the march, but in LB_F64 below 200000 sites or 6 rows (ny), and in
+ * LB_F32 and LB_F16 below 6 rows where the state exceeds 280 MB; with more
+ * sites per lane the march where ceil(nx/64) ceil(ny/8) ceil(nz/16) >= 256;
  * else the two-pass step. */
 #define LB_STEP_AUTO     0
 #define LB_STEP_MARCH    1

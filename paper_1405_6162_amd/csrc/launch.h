@@ -507,17 +507,27 @@ int run_binary_march(lb_ctx* c) {
 // Which binary step LB_STEP_AUTO takes.  One launch of the march beats the
 // two of the two-pass step (phi pass + fused collide, every site in parallel)
 // but on small FP64 lattices, whose few blocks each run a plane's gathers and
-// FP64 collision in sequence.  us a step, march / two-pass: FP64 48^3 24 / 22,
-// 64^3 34 / 39, 96^3 125 / 136; FP32 24^3 6.8 / 8.4, 48^3 14.9 / 14.6, 64^3 17 /
-// 22; FP16 24^3 7.3 / 8.4, 48^3 12.2 / 12.2, 96^3 47 / 54.
-// With more than one site per lane, which only the two-pass kernels have, from
-// the size up where one launch over whole tiles wins in any case.  The two
-// paths give the same bits.
+// FP64 collision in sequence.  us a step, march / two-pass:
+//          24^3        32^3        40^3        48^3        56^3        64^3        80^3        96^3        112^3
+//   FP64  12.0 / 9.6  13.0 / 10.4 14.3 / 14.3 19.6 / 18.3 24.7 / 27.9 31.1 / 33.1 82.1 / 87.2 125 / 135   177 / 203
+//   FP32   6.6 / 8.2   6.9 / 8.5   8.5 / 10.4 11.4 / 13.4 13.4 / 16.7 15.4 / 18.9 33.2 / 38.0 59.6 / 64.9  96 / 101
+//   FP16   7.1 / 8.2   7.3 / 8.2   8.1 / 9.9  11.3 / 11.8 12.3 / 13.9 12.4 / 14.6 27.9 / 29.9 34.1 / 39.8  45 / 53
+// Of 60 random FP64 boxes of 200000 to 1.9 million sites the march lost on five,
+// by 1 to 5%, and won by 9% on average.
+// Fewer than six rows leave much of a march block idle, whose wavefronts work all
+// the same: FP64 700 x 3 x 300 93 / 87, 700 x 5 x 200 102 / 97, 2048 x 1 x 256 142 /
+// 80; in the other storages beyond the cache (Cached): 4 x 4 x 16384 FP32 191 / 171,
+// FP16 186 / 158, 2 x 2 x 50000 FP32 411 / 325; within it 700 x 3 x 300 41 / 47.
+// With more than one site per lane, which only the two-pass kernels have, the
+// march runs from 256 blocks of at most 16 planes up: 512 x 512 x 4 with vvl 2 FP64
+// 131 / 147, FP32 67 / 73; 128^3 247 / 300.  The two paths give the same bits.
 template <class S>
 bool march_pays(const lb_ctx* c) {
     if (c->p.binary_step == LB_STEP_MARCH) return true;
     if (c->p.binary_step == LB_STEP_TWO_PASS) return false;
-    if (c->p.vvl > 1) return c->L.nsite >= (int64_t)128 * 128 * 128;
+    if (c->p.vvl > 1)
+        return (int64_t)tiles(c->p.nx, MarchTile::TX) * tiles(c->p.ny, MarchTile::TY) * tiles(c->p.nz, 16) >= kCUs;
+    if (c->p.ny < 6 && (sizeof(S) == 8 || !c->cached())) return false;
     return sizeof(S) != 8 || c->L.nsite >= 200000;
 }
 

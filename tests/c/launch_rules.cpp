@@ -2,6 +2,8 @@
 // rules (host code only; nothing is launched):
 //   chunks <columns> <nz> <slots>   -> the number of chunks of a marching kernel
 //   tried <columns> <nz> <slots>    -> the same by trying every count
+//   march <lattice>                 -> whether LB_STEP_AUTO marches (1) or takes the two-pass step (0)
+// with <lattice> = <storage> <collision> <vvl> <nx> <ny> <nz>, numbers of lb.h.
 #include <cstdio>
 #include <cstring>
 
@@ -17,13 +19,34 @@ static int tried(int64_t columns, int nz, int slots) {
     return chunks;
 }
 
+// A context of the lattice read from stdin, with no workspace.
+static bool read_lattice(int model, lb_ctx& c) {
+    lb_params p{};
+    if (std::scanf("%d %d %d %d %d %d", &p.storage, &p.collision, &p.vvl, &p.nx, &p.ny, &p.nz) != 6) return false;
+    p.model = model;
+    p.tau_f = p.tau_minus = p.tau_bulk = p.tau_ghost_even = p.tau_ghost_odd = 1.0;
+    p.mobility = p.gamma = 1.0;
+    if (lbl::check_params(&p) != LB_OK) return false;
+    c.p = p;
+    c.L = lbl::layout_of(&p);
+    return true;
+}
+
 int main() {
     char what[32];
-    long long a, b, c;
-    while (std::scanf("%31s %lld %lld %lld", what, &a, &b, &c) == 4) {
-        if (!std::strcmp(what, "chunks")) std::printf("%d\n", lbl::chunks_of(a, (int)b, (int)c));
-        else if (!std::strcmp(what, "tried")) std::printf("%d\n", tried(a, (int)b, (int)c));
-        else return 1;
+    while (std::scanf("%31s", what) == 1) {
+        long long a, b, s;
+        if (!std::strcmp(what, "chunks") || !std::strcmp(what, "tried")) {
+            if (std::scanf("%lld %lld %lld", &a, &b, &s) != 3) return 1;
+            std::printf("%d\n", *what == 'c' ? lbl::chunks_of(a, (int)b, (int)s) : tried(a, (int)b, (int)s));
+        } else if (!std::strcmp(what, "march")) {
+            lb_ctx c{};
+            if (!read_lattice(LB_BINARY, c)) return 1;
+            std::printf("%d\n", c.p.storage == LB_F64 ? lbl::march_pays<double>(&c)
+                                : c.p.storage == LB_F32 ? lbl::march_pays<float>(&c) : lbl::march_pays<_Float16>(&c));
+        } else {
+            return 1;
+        }
     }
     return 0;
 }

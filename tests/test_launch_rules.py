@@ -41,3 +41,20 @@ def test_chunks_of_a_long_lattice_take_no_time(ask):
     """The count is looked for at every launch: 300 launches on lattices of up
     to 5e8 planes within 10 s (trying every count takes about 1 s each)."""
     ask(["chunks %d %d 256" % (1 + k % 3, 500000000 // (1 + k % 7)) for k in range(300)], timeout=10)
+
+
+F64, F32, F16 = 0, 1, 2
+
+
+@pytest.mark.parametrize("storage,vvl,shape,march", [
+    # small FP64 lattices take the two-pass step, others march
+    (F64, 0, (56, 56, 56), 0), (F64, 1, (64, 64, 64), 1), (F64, 0, (256, 256, 256), 1), (F64, 0, (512, 512, 1), 1),
+    (F32, 0, (8, 8, 8), 1), (F16, 0, (24, 24, 24), 1), (F16, 0, (384, 384, 384), 1),
+    # few rows: the two-pass step in FP64, and beyond the cache in the others
+    (F64, 0, (700, 3, 300), 0), (F64, 0, (700, 5, 200), 0), (F64, 0, (2048, 1, 256), 0), (F64, 0, (700, 6, 200), 1),
+    (F32, 0, (700, 3, 300), 1), (F32, 0, (4, 4, 16384), 0), (F16, 0, (2, 2, 4000000), 0), (F32, 0, (4, 6, 16384), 1),
+    # more than one site per lane: from 256 blocks of at most 16 planes
+    (F64, 2, (512, 512, 4), 1), (F32, 4, (512, 512, 4), 1), (F64, 4, (64, 64, 64), 0), (F16, 2, (112, 112, 112), 0),
+    (F32, 2, (128, 128, 128), 1), (F64, 2, (2048, 1, 256), 1)])
+def test_binary_step_taken(ask, storage, vvl, shape, march):
+    assert ask(["march %d 0 %d %d %d %d" % ((storage, vvl) + shape)]) == [str(march)]
