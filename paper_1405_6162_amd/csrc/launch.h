@@ -411,8 +411,8 @@ void by_collision(const lb_ctx* c, F&& fn) {
 // binary 1927 / 2022, FP32 320^3 binary 1881 / 1960, 512 x 512 x 24 367 / 388; one
 // round, FP64 256^3 binary 1864 / 1820, single 505 / 479, 128^3 256 / 245, FP32
 // 256^3 932 / 907.  FP32 pairs and FP16 show no rule (-5 to +3%) and keep XCD order.
-// So do the march's chunks of 3 to 15 planes: they are no sweep worth the name,
-// and what their ends read again comes from an XCD's own L2 (march_order).
+// So do the march's short chunks: they are no sweep worth the name, and what their
+// ends read again comes from an XCD's own L2 (march_order).
 inline unsigned march_grid(const Geo& g, int slots, bool launch_order) {
     const int n = g.nblocks;
     if (launch_order && n > slots) return (unsigned)(n % 8 != 0 ? n : n + 1);
@@ -420,14 +420,16 @@ inline unsigned march_grid(const Geo& g, int slots, bool launch_order) {
 }
 
 // Whether the march's tiles go in launch order where they need several rounds.
-// us a step, launch / XCD order: FP32 512 x 512 x 4 79.7 / 70.3, x 12 193.4 / 189.0,
-// 1024 x 1024 x 4 272 / 260, FP64 512 x 512 x 4 138 / 133; one and two planes go
-// either way (FP32 2048 x 2048 x 2 500 / 522, FP64 1061 / 1041), and so do pairs at
-// every depth (FP64 512 x 512 x 4 40.8 / 42.2, x 2 24.7 / 21.2).
+// us a step, launch / XCD order: chunks of 3 to 15 planes FP32 512 x 512 x 4 79.7 /
+// 70.3, x 12 193.4 / 189.0, 1024 x 1024 x 4 272 / 260, FP64 512 x 512 x 4 138 / 133; two
+// planes FP64 1024 x 1024 x 2 283 / 269, FP32 2048 x 2048 x 2 500 / 519; one plane FP32
+// 2048 x 2048 276 / 285, FP64 560 / 559; within the cache FP32 512 x 512 x 2 35.7 / 29.0,
+// 512 x 512 20.4 / 18.8.  Pairs go either way at every depth (FP64 512 x 512 x 4 40.8 /
+// 42.2, x 2 24.7 / 21.2).
 template <class S>
-bool march_order(const Geo& g) {
+bool march_order(const lb_ctx* c, const Geo& g) {
     const int depth = tiles(g.nz, g.gz);
-    return sizeof(S) > 2 && (depth < 3 || depth > 15);
+    return sizeof(S) > 2 && (depth > 15 || (depth < (sizeof(S) == 8 ? 2 : 3) && !c->cached()));
 }
 
 // One march from the pending state (fs, gs) to (fd, gd), all in the layout of
@@ -453,7 +455,7 @@ int launch_march(lb_ctx* c, const S* fs, const S* gs, S* fd, S* gd, bool canonic
         Timed t(c, LB_K_COLLIDE);
         by_collision(c, [&](auto coll) {
             k_binary_march<TP, S, PHI_OUT, decltype(coll)::value, BLK, decltype(ahead)::value>
-                <<<march_grid(g, march_slots<S>(), march_order<S>(g)), TP::TPB, 0, c->stream>>>(fs, gs, fd, gd, g, cp, phi);
+                <<<march_grid(g, march_slots<S>(), march_order<S>(c, g)), TP::TPB, 0, c->stream>>>(fs, gs, fd, gd, g, cp, phi);
         });
     };
     // records and structure-of-arrays states are far larger than the cache
