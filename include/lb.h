@@ -187,11 +187,11 @@ int lb_propagate(lb_ctx* ctx);
 /* nsteps x (collide; propagate).  nsteps == 0 is a no-op, < 0 is LB_EINVAL.
  * Each step is one launch of a fused pull-stream + collide kernel.  For
  * LB_SINGLE with vvl 0 or 1, lattices from 130000 (LB_F64), 200000 (LB_F32)
- * or 2000000 (LB_F16, nx a multiple of 64 and ny of 8) sites take their steps
- * two to a launch, the state between them staying on chip (an odd last step
- * runs alone; with LB_MRT in LB_F32 from 800000 sites and never in LB_F16,
- * whose 64-wide tiles also want LB_BGK and a chip nine tenths full); the bits are the same, and LB_K_COLLIDE then counts a pair as
- * one launch.  For LB_BINARY it is the single-pass march, which sums phi from
+ * or 2000000 (LB_F16) sites take their steps two to a launch, the state
+ * between them staying on chip, where that is faster: not on lattices of few
+ * planes or rows, nor with collisions that cost more than the bytes they save
+ * (an odd last step runs alone).  The bits are the same, and LB_K_COLLIDE then
+ * counts a pair as one launch.  For LB_BINARY it is the single-pass march, which sums phi from
  * the pulled g and takes its stencils on chip, or (small FP64 lattices,
  * LB_STEP_TWO_PASS) a phi kernel, then the fused collide (see binary_step).
  * Captured into a graph on a pending state, an even number of steps leaves

@@ -68,12 +68,10 @@ constexpr int march_slots() { return kCUs * MarchHold<S, 0>::waves * 4 * 64 / Ma
 // FP32 and FP16 (128 VGPRs): two blocks of 64 x 8 or, where 128-wide rows
 // leave no more lanes idle, one of 128 x 8 (256^3: 490 against 559 us a pair
 // in FP32, 355 against 384 in FP16).
-// From kPairMinSites up a pair beats two single steps, whose blocks each do
-// one plane where a pair's lead in and out over three; in FP16, whose pair is
-// bound by its arithmetic, only with no lanes idle besides.  us a step, in
-// pairs / single: FP64 48^3 8.8 / 8.6, 64^3 11.3 / 17.0, 256^3 478 / 896; FP32
-// 64^3 6.6 / 9.4, 256^3 250 / 453; FP16 112^3 24.5 / 24.4, 200 x 204 x 100 70.7 /
-// 67.3, 128^3 27.0 / 30.3, 256^3 177 / 225.
+// From kPairMinSites up a pair can beat two single steps (pair_pays).  us a step,
+// in pairs / single: FP64 48^3 8.8 / 8.6, 64^3 11.3 / 12.9, 256^3 480 / 896; FP32
+// 64^3 7.0 / 7.2, 256^3 250 / 450; FP16 112^3 24.5 / 24.4, 128^3 24.3 / 23.6, 256^3
+// 174 / 224.
 template <class S>
 constexpr int64_t kPairMinSites = sizeof(S) == 8 ? 130000 : (sizeof(S) == 4 ? 200000 : 2000000);
 using PairTile = Tiling<64, 8, 1, false, true, true>;
@@ -655,16 +653,67 @@ int launch_single_pair(lb_ctx* c, bool pending, const S* src, S* mid, S* dst, bo
     return launch_status();
 }
 
-// Whether two single-fluid steps run as one launch: not with more than one
-// site per lane (lb_params.vvl), nor on lattices too small.
+// Whether two single-fluid steps run as one launch.  A single step moves its bytes
+// at the rate of a copy, a pair half of them, but its lanes do step one also in
+// the planes a chunk leads in and out over, and do all of their work where they
+// are idle.  Lanes a site, with the idle rows of a tile, which load nothing of
+// their own, at three quarters: x * (1 + 3/4 (y - 1)) * z.  us a step, pair /
+// single, by lanes a site at nz of 1 to 8 planes of 2048 x 2048 (1024 x 1024 x 8):
+//                3           2           1.67        1.5         1.25        gain up to
+//   FP64 BGK  228 / 224   378 / 444   495 / 679   598 / 885   286 / 447     2.7
+//        TRT  242 / 224   391 / 442   513 / 676   616 / 881   295 / 448     2.5
+//        MRT  282 / 224   424 / 443   568 / 677   708 / 882   328 / 445     2.05
+//   FP32 BGK  102 / 114   170 / 226   237 / 343   300 / 445   145 / 225     3.05
+//        TRT  112 / 114   177 / 226   243 / 343   310 / 445   148 / 225     2.9
+//        MRT  152 / 115   222 / 226   297 / 343   373 / 443   168 / 225     2
+//   FP16 BGK   93 / 56    134 / 112   179 / 168   231 / 222   103 / 110     1.4
+//        TRT  116 / 56    164 / 114   216 / 169   267 / 221   118 / 111     1.15 (256^3 204 / 225)
+// (few rows: FP64 BGK 2048 x 1 x 256 52 / 24, 2 rows 64 / 60, 3 71 / 88, 4 77 / 114).
+// Rows shorter than a wavefront cost a single step time as well, by 0.43 a lane:
+// FP64 4 x 8 x 16384 148 / 183, 16 x 16 x 2048 41 / 50, 4 x 4 x 16384 114 / 96; beyond
+// the cache, rows that end within a 64-site block about another 128 bytes each:
+// FP32 60 x 2 x 40000 160 / 196, FP64 MRT 65 x 130 x 70 42 / 46.
+// A state in the cache whose blocks run all at once is bound by latency, and a pair
+// has half the launches.  BGK pairs there from three rows up: FP64 64 x 8 x 255
+// 7.4 / 8.7, 256 x 512 x 1 7.3 / 7.6, 64 x 2 x 2000 17.6 / 12.5; TRT up to 2.9 lanes:
+// FP64 256 x 256 x 2 9.3 / 8.8, 64^3 11.9 / 12.7, 72^3 19.9 / 20.1; in FP32 from 550000
+// sites: 80^3 14.9 / 14.0, 84^3 15.3 / 16.5; MRT in FP64 up to 1.9: 64^3 14.1 / 13.0,
+// 80^3 28.3 / 24.4, 128 x 128 x 32 21.5 / 24.0; in FP32 with 64-wide tiles from 800000
+// sites: 150 x 70 x 90 26.8 / 28.1, 192 x 96 x 30 14.6 / 13.8; 96^3, 128 wide, 26.2 /
+// 21.7, 104^3 30.2 / 28.9; beyond the cache 128^3 43.8 / 59.4.
+// FP16's pair, bound by its arithmetic, wants no lanes idle besides, and with
+// 64-wide tiles a chip nine tenths full: BGK 192^3 86 / 93, TRT 93 / 92; 200 x 204 x
+// 100 70.7 / 67.3.  MRT never there: 128^3 43 / 31.
 template <class S>
 bool pair_pays(const lb_ctx* c) {
-    if (c->p.model != LB_SINGLE || c->p.vvl > 1 || c->L.nsite < kPairMinSites<S>) return false;
-    if (sizeof(S) == 4 && c->p.collision == LB_MRT) return c->L.nsite >= 800000;
-    if (sizeof(S) > 2) return true;
-    if (c->p.collision == LB_MRT || c->p.nx % PairTile::TX != 0 || c->p.ny % PairTile::TY != 0) return false;
-    const int slots = pair_slots<S, PairTile>(), n = c->template column_geo<PairTile>(slots).nblocks;
-    return c->wide_rows() || (c->p.collision == LB_BGK && n * 10 >= (n + slots - 1) / slots * slots * 9);
+    const lb_params& p = c->p;
+    const int64_t n = c->L.nsite;
+    constexpr int t = sizeof(S) == 8 ? 0 : (sizeof(S) == 4 ? 1 : 2);
+    if (p.model != LB_SINGLE || p.vvl > 1 || n < kPairMinSites<S>) return false;
+    if (p.collision == LB_MRT && (t == 2 || (t == 1 && n < 800000))) return false;
+    if (t == 2 && (p.nx % PairTile::TX != 0 || p.ny % PairTile::TY != 0)) return false;
+    auto pays = [&](auto tiling) {
+        using TP = decltype(tiling);
+        constexpr int slots = pair_slots<S, TP>();
+        const Geo g = c->template column_geo<TP>(slots);
+        if (t == 2 && TP::TX == 64 &&
+            (p.collision != LB_BGK || g.nblocks * 10 < (g.nblocks + slots - 1) / slots * slots * 9))
+            return false;
+        const bool resident = g.nblocks <= slots && c->cached();
+        if (resident && t < 2 && p.collision == LB_BGK) return p.ny >= 3;
+        if (resident && t == 1 && p.collision == LB_TRT && n < 550000) return false;
+        const double x = (double)g.gx * TP::TX / p.nx, y = (double)g.gy * TP::TY / p.ny, z = 1.0 + 2.0 * g.gz / p.nz;
+        static constexpr double beyond[3][3] = {{2.7, 2.5, 2.05}, {3.05, 2.9, 2.0}, {1.4, 1.15, 0.0}};
+        static constexpr double within[2][3] = {{0.0, 2.9, 1.9}, {0.0, 2.9, TP::TX == 64 ? 2.0 : 0.0}};
+        const double limit = resident && t < 2 ? within[t % 2][p.collision] : beyond[t][p.collision];
+        double row = 0.43 * tiles(p.nx, 64) * 64 / p.nx;
+        if (!c->cached() && p.nx > 32 && p.nx % 64 != 0) row = std::max(row, 1.0 + 128.0 / (p.nx * sizeof(S)));
+        return x * (1.0 + 0.75 * (y - 1.0)) * z <= limit * std::max(1.0, row);
+    };
+    if constexpr (sizeof(S) < 8) {
+        if (c->wide_rows()) return pays(PairTileWide{});
+    }
+    return pays(PairTile{});
 }
 
 // Whether the context's stream is being captured into a graph (the null

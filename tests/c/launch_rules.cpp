@@ -3,6 +3,7 @@
 //   chunks <columns> <nz> <slots>   -> the number of chunks of a marching kernel
 //   tried <columns> <nz> <slots>    -> the same by trying every count
 //   march <lattice>                 -> whether LB_STEP_AUTO marches (1) or takes the two-pass step (0)
+//   pair <lattice>                  -> whether single-fluid steps run two to a launch
 // with <lattice> = <storage> <collision> <vvl> <nx> <ny> <nz>, numbers of lb.h.
 #include <cstdio>
 #include <cstring>
@@ -44,6 +45,11 @@ int main() {
             if (!read_lattice(LB_BINARY, c)) return 1;
             std::printf("%d\n", c.p.storage == LB_F64 ? lbl::march_pays<double>(&c)
                                 : c.p.storage == LB_F32 ? lbl::march_pays<float>(&c) : lbl::march_pays<_Float16>(&c));
+        } else if (!std::strcmp(what, "pair")) {
+            lb_ctx c{};
+            if (!read_lattice(LB_SINGLE, c)) return 1;
+            std::printf("%d\n", c.p.storage == LB_F64 ? lbl::pair_pays<double>(&c)
+                                : c.p.storage == LB_F32 ? lbl::pair_pays<float>(&c) : lbl::pair_pays<_Float16>(&c));
         } else {
             return 1;
         }

@@ -58,3 +58,35 @@ F64, F32, F16 = 0, 1, 2
     (F32, 2, (128, 128, 128), 1), (F64, 2, (2048, 1, 256), 1)])
 def test_binary_step_taken(ask, storage, vvl, shape, march):
     assert ask(["march %d 0 %d %d %d %d" % ((storage, vvl) + shape)]) == [str(march)]
+
+
+BGK, TRT, MRT = 0, 1, 2
+
+
+@pytest.mark.parametrize("storage,coll,shape,pair", [
+    # few planes: a pair's chunks lead in and out over more than they keep
+    (F64, BGK, (2048, 2048, 1), 0), (F64, BGK, (2048, 2048, 2), 1), (F64, MRT, (2048, 2048, 1), 0),
+    (F64, MRT, (2048, 2048, 2), 1), (F32, BGK, (2048, 2048, 1), 1), (F32, TRT, (2048, 2048, 1), 0),
+    (F32, MRT, (2048, 2048, 1), 0), (F16, BGK, (2048, 2048, 4), 0), (F16, BGK, (1024, 1024, 8), 1),
+    (F16, TRT, (1024, 1024, 8), 0), (F64, BGK, (512, 512, 1), 0), (F64, TRT, (1024, 512, 1), 0),
+    # few rows, and rows shorter than a wavefront
+    (F64, BGK, (2048, 1, 256), 0), (F64, BGK, (2048, 2, 256), 0), (F64, BGK, (2048, 3, 256), 1),
+    (F64, MRT, (2048, 3, 256), 0), (F64, BGK, (64, 2, 2000), 0), (F64, BGK, (64, 3, 2000), 1),
+    (F32, BGK, (300, 2, 400), 0), (F64, BGK, (4, 4, 16384), 0), (F64, BGK, (4, 8, 16384), 1),
+    (F64, BGK, (2, 2, 50000), 0), (F32, BGK, (2, 2, 4000000), 0), (F64, BGK, (16, 16, 2048), 1),
+    (F32, TRT, (4, 8, 16384), 1), (F32, BGK, (60, 2, 40000), 1), (F64, MRT, (65, 130, 70), 1),
+    # in the cache, all blocks at once
+    (F64, BGK, (64, 8, 255), 1), (F64, TRT, (256, 256, 2), 0), (F64, TRT, (64, 64, 64), 1),
+    (F64, MRT, (64, 64, 32), 0), (F64, MRT, (64, 64, 64), 0), (F64, MRT, (128, 128, 32), 1),
+    (F32, TRT, (80, 80, 80), 0), (F32, TRT, (88, 88, 88), 1), (F32, MRT, (64, 64, 64), 0), (F32, MRT, (104, 104, 104), 0),
+    # the cubes
+    (F64, BGK, (48, 48, 48), 0), (F64, BGK, (256, 256, 256), 1), (F64, MRT, (256, 256, 256), 1),
+    (F32, MRT, (128, 128, 128), 1), (F32, MRT, (150, 70, 90), 1), (F16, BGK, (128, 128, 128), 1),
+    (F16, TRT, (128, 128, 128), 0), (F16, TRT, (256, 256, 256), 1), (F16, MRT, (256, 256, 256), 0),
+    (F16, BGK, (200, 204, 100), 0)])
+def test_pairs_taken(ask, storage, coll, shape, pair):
+    assert ask(["pair %d %d 0 %d %d %d" % ((storage, coll) + shape)]) == [str(pair)]
+
+
+def test_no_pairs_with_more_than_one_site_per_lane(ask):
+    assert ask(["pair 0 0 2 256 256 256"]) == ["0"]
