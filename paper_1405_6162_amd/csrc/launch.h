@@ -34,10 +34,11 @@ using Pol = Tiling<64, 4, 1, false, true, true>;
 // single fluid in pairs FP32 96^3 15.6 / 19.7, 112^3 22.9 / 30.0, one at a time
 // FP64 64^3 12.9 / 17.0; beyond the cache they lose: FP64 128^3 261 / 247, 256^3
 // 1919 / 1819.  So they do where a single fluid's state fits the eight 4 MB L2
-// caches (kL2Bytes; BGK and TRT three quarters of them), which have to write
+// caches (kL2Bytes; BGK and TRT seven eighths of them), which have to write
 // back what they hold after every launch: FP16 BGK 64^3 (20 MB) 5.4 / 5.2, 320 x 320
-// x 2 (16 MB) 5.8 / 4.9, MRT 60^3 7.5 / 6.3, FP32 56^3 (30 MB) MRT 6.9 / 6.2, BGK
-// 6.1 / 6.9; 64^3 (40 MB) MRT 8.2 / 9.3.  The march gains at all sizes.
+// x 2 (16 MB) 5.8 / 4.9, 64 x 53 x 96 (25 MB) 6.3 / 5.9, MRT 60^3 7.5 / 6.3, FP32 56^3
+// (30 MB) MRT 6.9 / 6.2, BGK 6.1 / 6.9; 64^3 (40 MB) MRT 8.2 / 9.3.  The march gains at
+// all sizes.
 template <class P> using Cached = Tiling<P::TX, P::TY, P::TZ, P::nt_load, false, P::xcd>;
 // The same for blocked states of 4 GiB and more a buffer (layout_of).
 template <class P> using Wide = Tiling<P::TX, P::TY, P::TZ, P::nt_load, P::nt_store, P::xcd, true>;
@@ -274,7 +275,7 @@ struct lb_ctx {
     // Whether ordinary stores keep the state where the next step reads it (see Cached).
     bool cached() const {
         if (p.model == LB_BINARY) return 4 * L.dist_bytes <= lbl::kCachedBytes;
-        const size_t least = p.collision == LB_MRT ? lbl::kL2Bytes : lbl::kL2Bytes / 4 * 3;
+        const size_t least = p.collision == LB_MRT ? lbl::kL2Bytes : lbl::kL2Bytes / 8 * 7;
         return 2 * L.dist_bytes > least && 2 * L.dist_bytes <= lbl::kCachedBytes;
     }
     // The same for copies between the state and the caller's arrays, of which one
