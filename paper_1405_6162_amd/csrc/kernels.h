@@ -467,27 +467,30 @@ __device__ __forceinline__ int wrap_plane(int z, int nz) {
 // load's immediate offset); what is left to a lane is the 32-bit offset of
 // its nine (x, y) neighbours, formed once.  A pull is then a single
 // instruction with no vector arithmetic, and only a plane, not a buffer, has
-// to stay below 4 GiB.  The empty asm statements keep the compiler from
+// to stay below 4 GiB (FP32 planes beyond take a vector add a load).  The empty asm statements keep the compiler from
 // moving parts of the sum back into per-lane 64-bit registers (FP32 march:
 // 123 VGPRs with them, 137 before).
 #define LB_GLOBAL __attribute__((address_space(1)))
 
 // Byte offsets of (x, y) and its neighbours in a plane, element 3 (dy + 1) + dx + 1.
+// WIDE (4-byte elements under a policy with `wide`): element offsets, for blocked
+// planes of 4 GiB and more.
 struct InPlane { uint32_t at[9]; };
+template <class P, class S> constexpr bool wide_plane = sizeof(S) == 4 && P::wide;
 
-template <class S>
+template <class S, bool WIDE>
 __device__ __forceinline__ InPlane in_plane(int x, int y, const Geo& g) {
     const uint32_t xs[3] = {(uint32_t)(x == 0 ? g.nx - 1 : x - 1), (uint32_t)x, (uint32_t)(x + 1 >= g.nx ? 0 : x + 1)};
     const uint32_t ys[3] = {(uint32_t)(y == 0 ? g.ny - 1 : y - 1), (uint32_t)y, (uint32_t)(y + 1 >= g.ny ? 0 : y + 1)};
     InPlane r;
 #pragma unroll
     for (int k = 0; k < 9; ++k)
-        r.at[k] = (ys[k / 3] * g.ys + (xs[k % 3] >> 6) * g.xbs + (xs[k % 3] & 63u)) * (uint32_t)sizeof(S);
+        r.at[k] = (ys[k / 3] * g.ys + (xs[k % 3] >> 6) * g.xbs + (xs[k % 3] & 63u)) * (uint32_t)(WIDE ? 1 : sizeof(S));
     return r;
 }
 
-// Plane z of a distribution: direction i of the element at byte offset o.
-template <class S, bool BLK>
+// Plane z of a distribution: direction i of the element at offset o (InPlane).
+template <class S, bool BLK, bool WIDE>
 struct PlaneBase {
     static constexpr int N = BLK ? (Q * 64 * (int)sizeof(S) + 4095) / 4096 : 1;
     const LB_GLOBAL char* p[N];
@@ -504,7 +507,8 @@ struct PlaneBase {
     template <int I>
     __device__ __forceinline__ const LB_GLOBAL S* dir(uint32_t o) const {
         constexpr int by = I * 64 * (int)sizeof(S);
-        if constexpr (BLK) return (const LB_GLOBAL S*)(p[by / 4096] + o + by % 4096);
+        if constexpr (BLK && WIDE) return (const LB_GLOBAL S*)(p[by / 4096] + by % 4096) + o;
+        else if constexpr (BLK) return (const LB_GLOBAL S*)(p[by / 4096] + o + by % 4096);
         else return (const LB_GLOBAL S*)(p[0] + I * stride + o);
     }
 };
@@ -513,9 +517,9 @@ struct PlaneBase {
 // from a pending distribution, or its own of a direct one.
 template <class P, class S, bool BLK, bool GATHER = true>
 __device__ __forceinline__ void pull_plane(const S* src, int z, const Geo& g, InPlane ip, S (&v)[Q]) {
-    const PlaneBase<S, BLK> pl[3] = {PlaneBase<S, BLK>(src, z == 0 ? g.nz - 1 : z - 1, g),
-                                     PlaneBase<S, BLK>(src, z, g),
-                                     PlaneBase<S, BLK>(src, z + 1 >= g.nz ? 0 : z + 1, g)};
+    using Plane = PlaneBase<S, BLK, wide_plane<P, S>>;
+    const Plane pl[3] = {Plane(src, z == 0 ? g.nz - 1 : z - 1, g), Plane(src, z, g),
+                         Plane(src, z + 1 >= g.nz ? 0 : z + 1, g)};
 #pragma unroll
     for (int k = 0; k < 9; ++k) asm volatile("" : "+v"(ip.at[k]));
     static_for<0, Q>([&](auto I) {
@@ -585,8 +589,9 @@ __global__ __launch_bounds__(P::TPB, (MarchHold<S, AHEAD>::waves)) void k_binary
     // this lane's site of the ring around the tile, if any
     int rx, ry;
     const bool has_halo = ring_site<P, false>(k, rx, ry);
-    const InPlane own = in_plane<S>(x, y, geo),
-                  halo = in_plane<S>(image_of(tile.x0 + rx, geo.nx), image_of(tile.y0 + ry, geo.ny), geo);
+    constexpr bool WIDE = wide_plane<P, S>;
+    const InPlane own = in_plane<S, WIDE>(x, y, geo),
+                  halo = in_plane<S, WIDE>(image_of(tile.x0 + rx, geo.nx), image_of(tile.y0 + ry, geo.ny), geo);
     const uint32_t site = (uint32_t)y * (uint32_t)geo.nx + (uint32_t)x;      // in a canonical plane
     const int me = (ty + 1) * LX + tx + 1, at_halo = (ry + 1) * LX + rx + 1;  // LDS slots
 
@@ -665,7 +670,7 @@ __global__ __launch_bounds__(P::TPB, (MarchHold<S, AHEAD>::waves)) void k_binary
             const T pym = ring[r][me - LX], pyp = ring[r][me + LX];
             const T pzm = ring[slot(z - 1)][me], pzp = ring[slot(z + 1)][me];
             const Stencil<T> st(phic, pxm, pxp, pym, pyp, pzm, pzp);
-            const PlaneBase<S, BLK> fd(fdst, z, geo), gd(gdst, z, geo);
+            const PlaneBase<S, BLK, WIDE> fd(fdst, z, geo), gd(gdst, z, geo);
             uint32_t off = own.at[4];
             asm volatile("" : "+v"(off));
             collide_binary<COLL, S>(
@@ -729,11 +734,12 @@ __global__ __launch_bounds__(P::TPB, sizeof(S) == 8 ? 2 : 4) void k_single_pair(
     const bool active = (tile.x0 + tx < geo.nx) && (tile.y0 + ty < geo.ny);
     int rx, ry;
     const bool ring = ring_site<P, true>(t, rx, ry);
-    const InPlane own = in_plane<S>(image_of(tile.x0 + tx, geo.nx), image_of(tile.y0 + ty, geo.ny), geo),
-                  around = in_plane<S>(image_of(tile.x0 + rx, geo.nx), image_of(tile.y0 + ry, geo.ny), geo);
+    constexpr bool WIDE = wide_plane<P, S>;
+    const InPlane own = in_plane<S, WIDE>(image_of(tile.x0 + tx, geo.nx), image_of(tile.y0 + ty, geo.ny), geo),
+                  around = in_plane<S, WIDE>(image_of(tile.x0 + rx, geo.nx), image_of(tile.y0 + ry, geo.ny), geo);
     auto pull = [&](int z, const InPlane& ip, S (&v)[Q]) { pull_plane<P, S, BLK, GATHER>(src, z, geo, ip, v); };
     auto put = [&](S* to, int z, const S (&v)[Q]) {
-        const PlaneBase<S, BLK> pl(to, z, geo);
+        const PlaneBase<S, BLK, WIDE> pl(to, z, geo);
         uint32_t off = own.at[4];
         asm volatile("" : "+v"(off));
         static_for<0, Q>([&](auto I) {

@@ -40,7 +40,7 @@ using Pol = Tiling<64, 4, 1, false, true, true>;
 // (30 MB) MRT 6.9 / 6.2, BGK 6.1 / 6.9; 64^3 (40 MB) MRT 8.2 / 9.3.  The march gains at
 // all sizes.
 template <class P> using Cached = Tiling<P::TX, P::TY, P::TZ, P::nt_load, false, P::xcd>;
-// The same for blocked states of 4 GiB and more a buffer (layout_of).
+// The same for blocked states of 4 GiB and more a buffer, or an FP32 plane (layout_of).
 template <class P> using Wide = Tiling<P::TX, P::TY, P::TZ, P::nt_load, P::nt_store, P::xcd, true>;
 constexpr size_t kCachedBytes = 280000000;
 constexpr size_t kL2Bytes = 32000000;
@@ -95,6 +95,7 @@ struct Layout {
     int64_t dstride;        // elements between consecutive directions
     bool blocked;           // 64-site blocks holding their 19 directions together
     bool wide;              // blocked, with byte offsets beyond 32 bits
+    bool wide_plane;        // blocked FP32, with byte offsets within a plane beyond 32 bits
     uint32_t zs, ys, xbs;   // site-offset strides (Geo)
     size_t dist_bytes;      // one 19-direction buffer
     size_t phi_bytes;
@@ -147,14 +148,18 @@ inline Layout layout_of(const lb_params* p) {
     // offsets by element (Wide) and the marching ones, whose bases are per
     // plane, are as below 4 GiB: FP64 320^3 us a step, blocked / structure of
     // arrays, 3793 / 4050 binary.  A state with more than one site per lane
-    // keeps the arrays, as do planes of 4 GiB (PlaneBase).
+    // keeps the arrays.  Planes of 4 GiB are blocked in FP32, whose marching
+    // kernels then take element offsets, for the binary fluid (8192 x 8192 x 1
+    // 4590 / 4910, x 2 8753 / 9120); the single fluid's pairs gain more from byte
+    // offsets (8192 x 8192 x 2 3046 structure of arrays, 3607 blocked single steps).
     const uint64_t xblocks = (uint64_t)tiles(p->nx, 64);
     const uint64_t blocked_elems = (uint64_t)p->nz * (uint64_t)p->ny * xblocks * Q * 64;
     const size_t stride_bytes = round_up((size_t)L.nsite * es, kAlign) + kDirPadBytes;
     const size_t soa_bytes = round_up(stride_bytes * Q, kAlign);
     const uint64_t u32 = (uint64_t)1 << 32;
     const bool small_plane = blocked_elems / (uint64_t)p->nz * es < u32;   // PlaneBase's offsets
-    L.blocked = small_plane && (es == 4 ? blocked_elems : blocked_elems * es) < u32;
+    L.blocked = (es == 4 ? blocked_elems : blocked_elems * es) < u32 && (small_plane || p->model == LB_BINARY);
+    L.wide_plane = L.blocked && !small_plane;
     if (!L.blocked && small_plane && es != 4 && p->vvl <= 1)
         L.blocked = L.wide = blocked_elems < u32 && blocked_elems * es <= soa_bytes;
     if (L.blocked) {
@@ -461,6 +466,9 @@ int launch_march(lb_ctx* c, const S* fs, const S* gs, S* fd, S* gd, bool canonic
     auto launch = [&](auto tiling, auto ahead) {
         using TP = decltype(tiling);
         if constexpr (BLK && !PHI_OUT) {
+            if constexpr (sizeof(S) == 4) {
+                if (c->L.wide_plane) { with(Wide<TP>{}, ahead); return; }
+            }
             if (c->cached()) { with(Cached<TP>{}, ahead); return; }
             if constexpr (sizeof(S) > 2) {
                 const Geo g = c->template column_geo<TP>(march_slots<S>());

@@ -4,6 +4,7 @@
 //   tried <columns> <nz> <slots>    -> the same by trying every count
 //   march <lattice>                 -> whether LB_STEP_AUTO marches (1) or takes the two-pass step (0)
 //   pair <lattice>                  -> whether single-fluid steps run two to a launch
+//   layout <model> <lattice>        -> blocked, wide, wide_plane of lbl::Layout
 // with <lattice> = <storage> <collision> <vvl> <nx> <ny> <nz>, numbers of lb.h.
 #include <cstdio>
 #include <cstring>
@@ -50,6 +51,11 @@ int main() {
             if (!read_lattice(LB_SINGLE, c)) return 1;
             std::printf("%d\n", c.p.storage == LB_F64 ? lbl::pair_pays<double>(&c)
                                 : c.p.storage == LB_F32 ? lbl::pair_pays<float>(&c) : lbl::pair_pays<_Float16>(&c));
+        } else if (!std::strcmp(what, "layout")) {
+            lb_ctx c{};
+            int model;
+            if (std::scanf("%d", &model) != 1 || !read_lattice(model, c)) return 1;
+            std::printf("%d %d %d\n", c.L.blocked, c.L.wide, c.L.wide_plane);
         } else {
             return 1;
         }

@@ -90,3 +90,24 @@ def test_pairs_taken(ask, storage, coll, shape, pair):
 
 def test_no_pairs_with_more_than_one_site_per_lane(ask):
     assert ask(["pair 0 0 2 256 256 256"]) == ["0"]
+
+
+SINGLE, BINARY = 0, 1
+
+
+@pytest.mark.parametrize("model,storage,vvl,shape,layout", [
+    # below 4 GiB a buffer: blocked (FP32, addressed by element, below 2^32 values)
+    (BINARY, F64, 0, (256, 256, 256), "1 0 0"), (BINARY, F32, 0, (384, 384, 384), "1 0 0"),
+    (SINGLE, F16, 4, (100, 90, 77), "1 0 0"),
+    # from 4 GiB: blocked with wide offsets where that needs no more room, which the workspace size (that of the
+    # structure of arrays) does not show; else the structure of arrays
+    (BINARY, F64, 0, (320, 320, 320), "1 1 0"), (SINGLE, F64, 1, (320, 320, 320), "1 1 0"),
+    (BINARY, F64, 2, (320, 320, 320), "0 0 0"), (BINARY, F64, 0, (330, 300, 310), "0 0 0"),
+    (BINARY, F16, 0, (512, 512, 440), "1 1 0"), (BINARY, F16, 0, (500, 500, 460), "0 0 0"),
+    (BINARY, F32, 0, (640, 640, 560), "0 0 0"),
+    # planes of 4 GiB
+    (BINARY, F32, 0, (8192, 8192, 1), "1 0 1"), (BINARY, F32, 4, (8192, 8192, 3), "1 0 1"),
+    (SINGLE, F32, 0, (8192, 8192, 1), "0 0 0"), (BINARY, F32, 0, (8192, 8192, 4), "0 0 0"),
+    (BINARY, F64, 0, (8192, 8192, 1), "0 0 0")])
+def test_state_layout(ask, model, storage, vvl, shape, layout):
+    assert ask(["layout %d %d 0 %d %d %d %d" % ((model, storage, vvl) + shape)]) == [layout]
