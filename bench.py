@@ -552,6 +552,18 @@ def bench_precision_single(args, n, desc, steps=500):
     print(json.dumps(out), flush=True)
 
 
+def launch_rates(bytes_per_site, nsite, steps, launches, kernel_ms, seconds):
+    """GB/s of `steps` steps in `launches` launches: "kernel", the bytes moved
+    over the kernels' time; "step", the same over the wall clock; and
+    "one_step_a_launch", what a launch a step would move over the wall clock.  A
+    launch reads and writes every value once whether it takes one step or two,
+    so only the last one counts each step's bytes, and no share of the peak is
+    formed from it."""
+    moved = bytes_per_site * nsite * launches
+    return {"kernel": moved / (kernel_ms * 1e-3) / 1e9 if launches else 0.0, "step": moved / seconds / 1e9,
+            "one_step_a_launch": bytes_per_site * nsite * steps / seconds / 1e9}
+
+
 def main():
     ap = argparse.ArgumentParser(description=__doc__.splitlines()[0])
     ap.add_argument("--gpus", type=int, default=1)
@@ -646,9 +658,8 @@ def main():
     seconds = wall
     mlups = nsite * args.steps / seconds / 1e6
     col_avg_ms = col_ms / max(col_n, 1)
-    # a single-fluid launch may hold two steps: bytes of all steps over all launches' time
-    achieved = alg["collide"] * nsite * args.steps / (col_ms * 1e-3) / 1e9 if col_n else 0.0
-    step_bytes = alg["collide"]
+    rates = launch_rates(alg["collide"], nsite, args.steps, col_n, col_ms, seconds)
+    achieved = rates["kernel"]
 
     out = {
         "metric": METRIC,
@@ -683,9 +694,10 @@ def main():
         },
         "pull_copy_ceiling": ceiling,
         "step_roofline": {
-            "bytes_per_site": step_bytes,
-            "GB/s": round(step_bytes * nsite * args.steps / seconds / 1e9, 1),
-            "frac": round(step_bytes * nsite * args.steps / seconds / 1e9 / HBM_PEAK_GBS, 4),
+            "bytes_per_site": round(alg["collide"] * col_n / args.steps, 2),
+            "GB/s": round(rates["step"], 1),
+            "frac": round(rates["step"] / HBM_PEAK_GBS, 4),
+            "one_step_a_launch_GB/s": round(rates["one_step_a_launch"], 1),
             "timing": "wall clock of the whole timed region",
             "event_ms_per_step": round(gpu_ms / args.steps, 5),
         },
