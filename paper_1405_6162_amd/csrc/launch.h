@@ -283,11 +283,12 @@ struct lb_ctx {
         const size_t least = p.collision == LB_MRT ? lbl::kL2Bytes : lbl::kL2Bytes / 8 * 7;
         return 2 * L.dist_bytes > least && 2 * L.dist_bytes <= lbl::kCachedBytes;
     }
-    // The same for copies between the state and the caller's arrays, of which one
-    // side is not read again: only where rows end within 64 bytes, which a
-    // nontemporal store then writes in parts.  us a copy out, ordinary /
-    // nontemporal: FP32 100^3 28.7 / 37.1, binary FP16 80^3 17.5 / 25.4; rows of
-    // whole 64 bytes FP32 64^3 6.1 / 5.2, 80^3 15.0 / 14.3, binary FP64 48^3 12.4 / 10.7.
+    // The same for copies from the state to the caller's arrays, which no step reads:
+    // only where rows end within 64 bytes, which a nontemporal store then writes in
+    // parts.  us a copy out, ordinary / nontemporal: FP32 100^3 28.7 / 37.1, binary
+    // FP16 80^3 17.5 / 25.4; rows of whole 64 bytes FP32 64^3 6.1 / 5.2, 80^3 15.0 / 14.3,
+    // binary FP64 48^3 12.4 / 10.7.  (Copies into the state are as its steps' stores:
+    // binary FP64 64^3, a record of one step, 62.0 / 68.4.)
     bool cached_copy() const { return cached() && (size_t)p.nx * lbl::storage_size(p.storage) % 64 != 0; }
     // Whether 128-wide tiles leave no more lanes of a row idle than 64-wide ones.
     bool wide_rows() const { return lbk::tiles(p.nx, 128) * 2 == lbk::tiles(p.nx, 64); }
@@ -396,6 +397,14 @@ int run_phi(lb_ctx* c) {
         return 0;
     });
     return launch_status();
+}
+
+// Whether the context's stream is being captured into a graph (the null
+// stream never is).
+inline bool capturing(const lb_ctx* c) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (c->stream && hipStreamIsCapturing(c->stream, &status) != hipSuccess) (void)hipGetLastError();
+    return status != hipStreamCaptureStatusNone;
 }
 
 // Calls fn with the context's collision as an integral constant.
@@ -611,8 +620,8 @@ int run_stream_into(lb_ctx* c, int src, S* f, S* g, const Geo& dgeo, bool cached
 }
 
 template <class S>
-int run_convert(lb_ctx* c, const S* fs, const S* gs, S* fd, S* gd, const Geo& sgeo, const Geo& dgeo) {
-    return run_copy<S, false>(c, fs, gs, fd, gd, sgeo, dgeo, c->cached_copy());
+int run_convert(lb_ctx* c, const S* fs, const S* gs, S* fd, S* gd, const Geo& sgeo, const Geo& dgeo, bool cached) {
+    return run_copy<S, false>(c, fs, gs, fd, gd, sgeo, dgeo, cached);
 }
 
 template <class S>
@@ -723,14 +732,6 @@ bool pair_pays(const lb_ctx* c) {
         if (c->wide_rows()) return pays(PairTileWide{});
     }
     return pays(PairTile{});
-}
-
-// Whether the context's stream is being captured into a graph (the null
-// stream never is).
-inline bool capturing(const lb_ctx* c) {
-    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-    if (c->stream && hipStreamIsCapturing(c->stream, &status) != hipSuccess) (void)hipGetLastError();
-    return status != hipStreamCaptureStatusNone;
 }
 
 // A step taken alone moves the state to the other buffer, but for the first
@@ -865,13 +866,14 @@ int run_get_state(lb_ctx* c, S* f, S* g) {
     if (c->pending) return run_stream_into<S>(c, c->cur, f, g, c->canonical_geo(), c->cached_copy());
     Timed t(c, LB_K_OTHER);
     return run_convert<S>(c, (const S*)c->fbuf(c->cur), (const S*)c->gbuf(c->cur), f, g, c->geo(),
-                          c->canonical_geo());
+                          c->canonical_geo(), c->cached_copy());
 }
 
 template <class S>
 int run_set_state(lb_ctx* c, const S* f, const S* g) {
     Timed t(c, LB_K_OTHER);
-    const int rc = run_convert<S>(c, f, g, (S*)c->fbuf(c->cur), (S*)c->gbuf(c->cur), c->canonical_geo(), c->geo());
+    const int rc = run_convert<S>(c, f, g, (S*)c->fbuf(c->cur), (S*)c->gbuf(c->cur), c->canonical_geo(), c->geo(),
+                                  c->cached());
     if (rc) return rc;
     c->pending = false;
     return LB_OK;
@@ -879,15 +881,29 @@ int run_set_state(lb_ctx* c, const S* f, const S* g) {
 
 // nsteps binary steps whose post-collision fields go to canonical memory, f
 // then g of step k to post + k*38*N; afterwards the state is pending on a copy
-// of the last of them, in the other buffer where it was pending before: the
-// buffer the record started from stays as it is, so a graph of the call records
-// the same steps at every replay.  Step 0 collides the context's state into post[0] (128^3:
+// of the last of them.  Captured on a pending state, the copy goes to the other
+// buffer: the one the record started from stays as it is, and a graph of the call
+// records the same steps at every replay.  (Always done, records of two steps
+// within the cache alternate between buffers: FP16 96^3 62 us, 55.)  Step 0 collides the context's state into post[0] (128^3:
 // 360 us with its phi; in the context's buffers and copied out it was 600);
 // later steps march from post[k-1] to post[k] (both of direction stride N).
+// A record of one step without its phi marches in the context's buffers and is
+// copied out, which spares the phi pass and the copy back: FP64 128^3 464 us, as
+// the others 509; 256^3 3589 and 4098; FP32 256^3 1795 and 1989.
 template <class S>
 int run_step_record_binary(lb_ctx* c, int32_t n, S* post, typename Compute<S>::T* phi) {
     using T = typename Compute<S>::T;
     const int64_t N = c->L.nsite;
+    if (n == 1 && !phi && c->pending && march_pays<S>(c)) {
+        int rc = run_binary_march<S>(c);
+        if (rc) return rc;
+        Timed t(c, LB_K_OTHER);
+        rc = run_convert<S>(c, (const S*)c->fbuf(c->cur), (const S*)c->gbuf(c->cur), post, post + Q * N, c->geo(),
+                            c->canonical_geo(), c->cached_copy());
+        if (rc) return rc;
+        c->pending = true;
+        return LB_OK;
+    }
     const auto cp = coll_params<S>(c);
     int rc = by_width(c, [&](auto pol) {              // step 0: phi of the state, then its collision
         using P = decltype(pol);
@@ -949,9 +965,9 @@ int run_step_record_binary(lb_ctx* c, int32_t n, S* post, typename Compute<S>::T
     {
         Timed t(c, LB_K_OTHER);
         const S* last = post + (size_t)(n - 1) * 2 * Q * N;
-        const int dst = c->pending ? 1 - c->cur : c->cur;
+        const int dst = c->pending && capturing(c) ? 1 - c->cur : c->cur;
         rc = run_convert<S>(c, last, last + Q * N, (S*)c->fbuf(dst), (S*)c->gbuf(dst), c->canonical_geo(),
-                            c->geo());
+                            c->geo(), c->cached());
         if (rc) return rc;
         c->cur = dst;
     }
@@ -1000,7 +1016,7 @@ int run_step_record(lb_ctx* c, int32_t n, S* post, typename Compute<S>::T* phi) 
     if (err) return err;
     Timed t(c, LB_K_OTHER);
     const int rc = run_convert<S>(c, post + (size_t)(n - 1) * Q * N, nullptr, (S*)c->fbuf(c->cur), nullptr, cg,
-                                  c->geo());
+                                  c->geo(), c->cached());
     if (rc) return rc;
     c->pending = true;
     return LB_OK;
