@@ -70,8 +70,8 @@ constexpr int march_slots() { return kCUs * MarchHold<S, 0>::waves * 4 * 64 / Ma
 // leave no more lanes idle, one of 128 x 8 (256^3: 490 against 559 us a pair
 // in FP32, 355 against 384 in FP16).
 // From kPairMinSites up a pair can beat two single steps (pair_pays).  us a step,
-// in pairs / single: FP64 48^3 8.8 / 8.6, 64^3 11.3 / 12.9, 256^3 480 / 896; FP32
-// 64^3 7.0 / 7.2, 256^3 250 / 450; FP16 112^3 24.5 / 24.4, 128^3 24.3 / 23.6, 256^3
+// in pairs / single: FP64 48^3 8.8 / 7.5, 64^3 11.1 / 12.9, 256^3 480 / 896; FP32
+// 64^3 7.0 / 7.2, 256^3 250 / 450; FP16 112^3 24.5 / 18.4, 128^3 24.3 / 23.9, 256^3
 // 174 / 224.
 template <class S>
 constexpr int64_t kPairMinSites = sizeof(S) == 8 ? 130000 : (sizeof(S) == 4 ? 200000 : 2000000);
@@ -147,7 +147,7 @@ inline Layout layout_of(const lb_params* p) {
     // structure of arrays (a lattice that fitted still does), the kernels take
     // offsets by element (Wide) and the marching ones, whose bases are per
     // plane, are as below 4 GiB: FP64 320^3 us a step, blocked / structure of
-    // arrays, 3793 / 4050 binary.  A state with more than one site per lane
+    // arrays, 3652 / 3966 binary.  A state with more than one site per lane
     // keeps the arrays.  Planes of 4 GiB are blocked in FP32, whose marching
     // kernels then take element offsets, for the binary fluid (8192 x 8192 x 1
     // 4590 / 4910, x 2 8753 / 9120); the single fluid's pairs gain more from byte
@@ -195,11 +195,10 @@ inline Layout layout_of(const lb_params* p) {
 // `slots` blocks at a time.  A chunk of d planes costs about d + 3 (its ends take
 // two planes of phi, or of step one, more): nz is cut, evenly, into the number
 // of chunks (at most 128 planes each) that makes rounds x (d + 3) least.
-// Measured against fixed depths: pair, 256^3 FP64, 926 us with 2 chunks (one
-// round), 1045 with 4; 128^3 128 with 8 (one round), 145 with 16.  March, FP64:
-// 96^3 115 us with 10 chunks (240 blocks), 148 with 6; 160^3 496 with 4 (one
-// round), 520 with 8; 64^3 31 with 32 chunks of 2 planes against 92 with 4 of 16
-// (the two-pass step: 40).
+// Measured against fixed counts, us a step, FP64: pairs 256^3 480 with 2 chunks
+// (one round), 512 with 4; 128^3 69 with 8 (one round), 80 with 16.  March 96^3
+// 126 with 10 chunks (240 blocks), 163 with 6; 160^3 496 with 4 (one round), 511
+// with 8; 64^3 31 with 32 chunks of 2 planes, 93 with 4 of 16.
 //
 // This runs at every launch, so it may not take time that grows with nz (1 x 1 x
 // 4e8, every count tried: 0.9 s a launch).  All counts from c to the last that
@@ -697,8 +696,8 @@ int launch_single_pair(lb_ctx* c, bool pending, const S* src, S* mid, S* dst, bo
 // FP64 256 x 256 x 2 9.3 / 8.8, 64^3 11.9 / 12.7, 72^3 19.9 / 20.1; in FP32 from 550000
 // sites: 80^3 14.9 / 14.0, 84^3 15.3 / 16.5; MRT in FP64 up to 1.9: 64^3 14.1 / 13.0,
 // 80^3 28.3 / 24.4, 128 x 128 x 32 21.5 / 24.0; in FP32 with 64-wide tiles from 800000
-// sites: 150 x 70 x 90 26.8 / 28.1, 192 x 96 x 30 14.6 / 13.8; 96^3, 128 wide, 26.2 /
-// 21.7, 104^3 30.2 / 28.9; beyond the cache 128^3 43.8 / 59.4.
+// sites: 150 x 70 x 90 27.0 / 28.4, 192 x 96 x 30 14.6 / 13.8; 96^3, 128 wide, 26.2 /
+// 21.7, 104^3 30.2 / 28.9; beyond the cache 128^3 44 / 59.
 // FP16's pair, bound by its arithmetic, wants no lanes idle besides, and with
 // 64-wide tiles a chip nine tenths full: BGK 192^3 86 / 93, TRT 93 / 92; 200 x 204 x
 // 100 70.7 / 67.3.  MRT never there: 128^3 43 / 31.
