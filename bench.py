@@ -100,13 +100,16 @@ def algorithmic_bytes(model, storage):
     return {"collide": 2 * 38 * es}
 
 
-def traffic_from_profile(workload):
+def traffic_from_profile(workload, kernel=""):
     """HBM bytes per launch of the dominant kernel from the committed
-    rocprofv3 counter summary, or None when there is none or the kernel
-    sources changed since it was taken."""
+    rocprofv3 counter summary, or None when there is none, the kernel
+    sources changed since it was taken or it counts another kernel than the
+    one that ran (with --vvl 2 and 4 a step is a launch of its own)."""
     from paper_1405_6162_amd import profsummary
     info = profsummary.read_traffic(os.path.join(ROOT, "profiles", "pmc_%s.txt" % workload))
     if not info or info.get("source_digest") != profsummary.kernel_source_digest():
+        return None
+    if kernel not in info["kernel"]:
         return None
     return int(float(info["traffic_bytes_per_launch"]))
 
@@ -660,6 +663,9 @@ def main():
     col_avg_ms = col_ms / max(col_n, 1)
     rates = launch_rates(alg["collide"], nsite, args.steps, col_n, col_ms, seconds)
     achieved = rates["kernel"]
+    kernel = ("k_binary_march (single-pass pull-stream + phi + collision)" if model == "binary"
+              else "k_single_pair (two fused pull-stream + collision steps a launch)" if col_n < args.steps
+              else "k_collide (fused pull-stream + collision)")
 
     out = {
         "metric": METRIC,
@@ -678,14 +684,12 @@ def main():
                    "storage": storage, "seed": 0, "sites_per_lane": args.vvl},
         "roofline": {
             "bound": "hbm",
-            "kernel": ("k_binary_march (single-pass pull-stream + phi + collision)" if model == "binary"
-                       else "k_single_pair (two fused pull-stream + collision steps a launch)" if col_n < args.steps
-                       else "k_collide (fused pull-stream + collision)"),
+            "kernel": kernel,
             "achieved": round(achieved, 1),
             "peak": HBM_PEAK_GBS,
             "unit": "GB/s",
             "frac": round(achieved / HBM_PEAK_GBS, 4),
-            "traffic": traffic_from_profile(args.workload),
+            "traffic": traffic_from_profile(args.workload, kernel.split()[0]),
             "bytes_per_site": alg["collide"],
             "avg_launch_ms": round(col_avg_ms, 5),
             "launches": col_n,
